@@ -211,7 +211,8 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
  * another on the stream and sharing the workspace, so rows Tt..Tt+T-1 give the same y as a call on those rows alone.
  * T = 32 on layers with one row scale per chunk (matrix-core kernel), else 16; T = 1 (B launches of the batch-1
  * kernels) for B <= 8 on mu = 8 layers with 8 or 16 fine salient row-scale groups per chunk (the s16 / s8
- * configurations), unless the batch_tile tuning asks for 16. fluxbin_plan_query reports T as batch_tile_rows.
+ * configurations) of fewer than 8 M weights (24 M at B = 2), unless the batch_tile tuning asks for 16.
+ * fluxbin_plan_query reports T as batch_tile_rows.
  * d_x fp16 with row stride ldx >= N (elements); d_y with row stride ldy >= M (elements of the output type). B = 1
  * gives the same result as fluxbin_lut_gemv.
  * Kernels: the LUT batch kernel (one set of tables per batch row; mu = 8, B <= 4 on layers with at least 2.25 (B = 2)
@@ -220,8 +221,11 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
  * units (the products are exact in the fp32 accumulation, as in the LUT path; the row scale is applied per 128-column
  * chunk); on layers of 2048 to 4096 rows, or of at most 8192 rows with at most 88 super-chunks (on a 256-CU device),
  * at B <= 8 the matrix-core kernel runs row-complete (every super-chunk of 16 or 32 rows in one workgroup, no split
- * reduction). Other layers with fine row-scale groups (g_r or g_s below 128), and those above at B > 8, run the
- * generic LUT kernel for B >= 2. All are deterministic; their results differ only by fp32 summation order.
+ * reduction). Large layers at B <= 8 and layers with 8 or 16 fine salient groups at mu = 8 run the matrix-core product
+ * in its block-scaled form (signs as fp4 operands; each 32-column block of x * colscale as a sum of fp6 digits that
+ * leaves at most 2^-29 of the block's largest product, below the rounding of the fp32 sums). Other layers with fine
+ * row-scale groups (g_r or g_s below 128) run the generic LUT kernel for B >= 2. All are deterministic; their results
+ * differ only by fp32 rounding and summation order.
  */
 fluxbin_status fluxbin_lut_gemm_smallbatch(const fluxbin_layer* layer, int32_t B, const uint16_t* d_x, int64_t ldx,
                                            void* d_y, int64_t ldy, int32_t y_is_fp32, void* d_workspace,
@@ -254,7 +258,8 @@ fluxbin_status fluxbin_lut_gemv_noalloc(const fluxbin_layer* layer, const uint16
  *   mfma_depth     FLUXBIN_MFMA_DEPTH     matrix-core kernel's units requested ahead (2 or 3); 0: 2
  *   early          FLUXBIN_EARLY          batch-1 request order (1: signs before the activations); -1: by layer size
  *   rpt            FLUXBIN_RPT            generic kernel rows per thread (1, 2, 4); 0: chosen by layer size
- *   mfma           FLUXBIN_MFMA           small-batch kernel: 1 matrix cores, 0 LUT tables; -1: chosen by B and size
+ *   mfma           FLUXBIN_MFMA           small-batch kernel: 1 matrix cores (fp16 form), 0 LUT tables; -1: chosen by B
+ *                                         and size (any non-default small-batch field also keeps the fp16 form)
  *   generic        FLUXBIN_GENERIC        1: the generic kernel for every batch size
  *   mfma_r2        FLUXBIN_MFMA_R2        0: matrix-core split tiles reduced by tile counters, not a second kernel
  *   bat_r2         FLUXBIN_BAT_R2         0: LUT batch kernel split tiles reduced by tile counters
@@ -281,7 +286,8 @@ fluxbin_status fluxbin_set_tuning(const fluxbin_tuning* t);
 
 /*
  * The launch plan a GEMV/GEMM call of batch B on this layer would use on the current device with the current tuning.
- *   kernel  0: batch-1 super-chunk kernel, 1: generic kernel, 2: LUT batch kernel (mu = 8), 3: matrix-core kernel,
+ *   kernel  0: batch-1 super-chunk kernel, 1: generic kernel, 2: LUT batch kernel (mu = 8), 3: matrix-core kernel
+ *           (fp16 form with 256-row tiles, block-scaled form with rows_per_tile 64 or 128),
  *           4: row-complete batch-1 kernel (layers with few rows; rows_per_tile 16, 32 or 48 rows per workgroup),
  *           5: row-complete matrix-core kernel (layers with few rows, B = 2..8).
  * Batches of more than batch_tile_rows rows (32 on layers the matrix-core kernel takes, else 16) run as batch_tiles

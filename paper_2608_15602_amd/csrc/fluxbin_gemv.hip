@@ -1225,6 +1225,8 @@ fluxbin_status launch_gemm(const fluxbin_layer& L, const Plan& p, int B, const u
     }
   } else if (p.kernel == 2) {
     ok = !fine && launch_gemm_batch(a, p.n_groups, p.depth, p.bg, p.reduce2, p.xv, stream);
+  } else if (p.mx_parts > 0) {
+    ok = fg >= 0 && launch_gemm_mx(a, p.bpad, int(L.shape.mu), fg, p.rows / 16, p.nt / 64, p.mx_parts, stream);
   } else if (p.kernel == 3) {
     ok = !fine && launch_gemm_mfma(a, p.bpad, int(L.shape.mu), p.depth, p.reduce2, stream);
   } else if (p.kernel == 5) {

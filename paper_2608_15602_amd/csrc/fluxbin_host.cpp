@@ -291,16 +291,37 @@ static uint64_t layer_counter_bytes(int64_t M) {
   return round_up256(uint64_t(ceil_div(M, 256) + 4) * uint64_t(kCounterStride) * 4u);
 }
 
+// Block-scaled matrix-core kernel (B = 2..16), with the default small-batch tuning only: the tuning fields select among
+// the other kernels and their plans.
+static bool mx_tuning(const fluxbin_tuning& tu) {
+  return !tu.generic && tu.mfma == -1 && tu.mfma_rows == -1 && tu.mfma_depth == 0 && tu.mfma_r2 == 1 &&
+         tu.batch_tile == 0 && tu.align == -1 && tu.blocks == 0 && tu.blocks_per_cu == 0;
+}
+
+// 8 or 16 fine salient row-scale groups per chunk at mu = 8 (the paper's s16 / s8 configurations).
+static bool salient_fine(const fluxbin_layer& L, const Derived& dv) {
+  return L.shape.mu == 8 && dv.Gcg == 1 && (dv.Gcs == 8 || dv.Gcs == 16);
+}
+
+// Layers with fine salient groups at 2 <= B <= 8: the block-scaled kernel in one launch, or B batch-1 launches. us per
+// call, batch-1 launches -> block-scaled kernel, s16 / s8: 4096x4096 B = 2 12.7 / 13.2 -> 14.6 / 14.7, B = 4 24.6 /
+// 25.6 -> 15.4 / 15.9, B = 8 48.4 / 49.2 -> 17.3 / 17.3; 5120x5120 B = 2 17.1 / 18.3 -> 16.7 / 17.3; 5120x13824 B = 2
+// 30.2 / 28.5 -> 23.4 / 25.4, B = 8 116.7 / 108.1 -> 31.2 / 32.1. So from three rows on, at two rows from 24 M weights
+// (between the two square shapes). Layers below 8 M weights stay with the batch-1 launches (1536x2048: faster at B = 2,
+// 9.0 against 13.1 us, slower from B = 4 on, 17.4 against 13.8; their one-row batch tiles are pinned by the tests).
+static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B, const fluxbin_tuning& tu) {
+  return mx_tuning(tu) && salient_fine(L, dv) && B >= 2 &&
+         L.shape.M * L.shape.N >= (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20);
+}
+
 // Rows of a full batch tile (calls with more batch rows run as several launches): 32 on layers the matrix-core kernel
 // takes (one row scale per chunk), whose sign decode then serves two 16-row MFMA tiles, else 16. Layers with 8 or 16
-// fine salient row-scale groups at mu = 8 (the paper's s16 / s8 configurations), which only the generic kernel takes at
-// B >= 2, run B <= 8 rows as B launches of the batch-1 kernels instead: faster on all eight App. E.4 s8 / s16 layers
-// at B = 2, 4 and 8 (us per call, generic kernel -> per-row batch-1 launches: 4096x4096 s8 B = 2 15.1 -> 12.1, B = 8
-// 59.5 -> 46.4; 5120x13824 s8 B = 2 55.7 -> 30.1, B = 8 139.5 -> 115.3). FLUXBIN_BATCH_TILE=16 keeps 16-row tiles.
+// fine salient row-scale groups at mu = 8 (the paper's s16 / s8 configurations) run B <= 8 rows as B launches of the
+// batch-1 kernels where the block-scaled matrix-core kernel is not faster. FLUXBIN_BATCH_TILE=16 keeps 16-row tiles (of
+// the generic kernel on those layers).
 static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int B) {
   const Derived dv = derive(L.shape);
-  if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && L.shape.mu == 8 && dv.Gcg == 1 &&
-      (dv.Gcs == 8 || dv.Gcs == 16))
+  if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && salient_fine(L, dv) && !mx_fine_small_batch(L, dv, B, tu))
     return 1;
   if (tu.generic || dv.Gcg > 1 || dv.Gcs > 1 || tu.mfma == 0 || tu.mfma_depth == 3 || tu.mfma_r2 == 0 ||
       tu.batch_tile == kMaxBatch)
@@ -325,7 +346,7 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   const Derived dv = derive(L.shape);
   const bool fine = dv.Gcg > 1 || dv.Gcs > 1;
   // the batch-1 instances for fine groups: salient side only, 8 or 16 groups per chunk (s = 16 or 8 at mu = 8)
-  const bool b1_fine_ok = L.shape.mu == 8 && dv.Gcg == 1 && (dv.Gcs == 8 || dv.Gcs == 16);
+  const bool b1_fine_ok = salient_fine(L, dv);
   p->nt = 256;
   int rw_rb = 1;
   if (B == 1 && !force_generic && allow_rows && use_rows(L, dv, cus, tu, &rw_rb)) {
@@ -367,6 +388,55 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->ws_image_off = p->ws_partials_off;   // no partial sums: the staging image follows the counter region
     p->ws_bytes = p->ws_image_off +
                   uint64_t(mfma_rows_image_dwords(dv.NCP, dv.ncg + (dv.NCP - L.shape.Kb * dv.ncg), p->bpad)) * 4u;
+    return FLUXBIN_OK;
+  }
+  // Block-scaled matrix-core kernel. Layers with fine salient groups, whose other kernel is the generic one: at 9 to 16
+  // rows always (us per call, generic -> this, s16 / s8: 128x256 15.5 -> 12.5 / 15.8 -> 15.9, 1024x1024 33.5 -> 13.7 /
+  // 33.5 -> 15.9, 4096x11008 203 -> 32.7 / 197 -> 35.8), at up to 8 rows (calls of that many rows, and the last rows of
+  // larger batches) from 2^19 weights (6 rows: 512x1024 13.6 -> about 12.5, 256x384 10.6 -> about 12.5). Layers with one row scale per chunk at B <= 8,
+  // where neither the LUT batch kernel nor the row-complete matrix-core kernel is chosen, from 270 tiles of 16 rows x
+  // 128 columns per CU: its image kernel and (with several workgroups per row tile) its reduction cost 5 to 9 us, its
+  // matrix part less than half of the fp16 kernel's. us per call, fp16 kernel -> this one, B = 8: 11008x4096 2+1 (180
+  // tiles per CU) 15.7 -> 16.2, 4096x11008 16.7 -> 17.7; 5120x13824 2 bases (270) 19.6 -> 17.9; 8192x8192 3+1 (392)
+  // 22.1 -> 21.2; 28672x8192 2+1 / 3+1 35.0 -> 28.8 / 48.1 -> 38.3; 57344x8192 2+1 63.0 -> 48.5; B = 2, mu = 4:
+  // 28672x8192 3+1 42.9 -> 29.2. At 9 to 16 rows (twice the instructions and digit bytes) it is no faster there: 49.8
+  // against 50.3.
+  if (B >= 2 && B <= kMaxBatch && mx_tuning(tu) &&
+      ((b1_fine_ok && (B > 8 || L.shape.M * L.shape.N >= (int64_t(1) << 19))) ||
+       (!fine && B <= 8 && use_mfma(L, B, cus, tu) &&
+        ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(270) * cus))) {
+    p->kernel = 3;
+    p->bg = B <= 2 ? 2 : (B <= 4 ? 4 : (B <= 8 ? 8 : 16));
+    p->bpad = p->bg;
+    p->n_groups = 1;
+    p->rpt = 1;
+    p->depth = 2;
+    // 64 (fine groups) or 128 rows per workgroup of eight wavefronts, one workgroup per CU; of four wavefronts, two per
+    // CU, where that fills the chip better (57344 rows: 448 workgroups; 20000 rows: 471 of 512 places against 157 of 256).
+    // As many workgroups per row tile as keep the launch one wave.
+    int waves = 8;
+    p->rows = b1_fine_ok ? 64 : 128;
+    p->n_tiles = ceil_div(L.shape.M, p->rows);
+    int64_t parts = cus / p->n_tiles > 1 ? cus / p->n_tiles : 1;
+    if (!b1_fine_ok) {
+      const int64_t parts4 = 2 * cus / p->n_tiles > 1 ? 2 * cus / p->n_tiles : 1;
+      if (p->n_tiles > cus || 10 * p->n_tiles * parts4 > 11 * 2 * p->n_tiles * parts) {
+        waves = 4;
+        parts = parts4;
+      }
+    }
+    const int64_t most = ceil_div(dv.NCP, waves);   // at least a chunk for every wavefront
+    if (parts > most) parts = most;
+    p->nt = 64 * waves;
+    p->units = p->n_tiles * L.NSC;
+    p->blocks = p->n_tiles * parts;
+    p->mx_parts = int(parts);
+    p->reduce2 = parts > 1;
+    p->ws_counters_off = 0;
+    p->ws_partials_off = layer_counter_bytes(L.shape.M);
+    const uint64_t part_bytes = parts > 1 ? uint64_t(parts) * uint64_t(B) * uint64_t(L.Mp) * 4u : 0u;
+    p->ws_image_off = round_up256(p->ws_partials_off + part_bytes);
+    p->ws_bytes = p->ws_image_off + uint64_t(dv.NCP) * uint64_t(mx_chunk_bytes(mx_instr(p->bpad)));
     return FLUXBIN_OK;
   }
   if (B == 1 && !force_generic && (!fine || b1_fine_ok)) {   // batch-1 kernel (mu = 8 or 4)

@@ -44,6 +44,12 @@ constexpr int64_t mfma_rows_lds_bytes(int64_t ncp, int64_t nblk, int bp) {
               ? ncp * 64 + nblk * 16 * (4 * bp + 4) + 64
               : mfma_rows_image_dwords(ncp, nblk, bp)) * 4;
 }
+// Block-scaled matrix-core kernel (B = 2..16): fp6 digits per activation product, instructions per 128-column chunk with
+// nbp padded batch rows (16 / nbp digits each), and bytes of a chunk's digit image (T operands of 64 lanes x 24 bytes
+// and the lanes' scale bytes).
+constexpr int kMxDigits = 6;
+constexpr int mx_instr(int nbp) { return (kMxDigits * nbp + 15) / 16; }
+constexpr int64_t mx_chunk_bytes(int t) { return 1536 * t + 256 * (t > 4 ? 2 : 1); }
 // Tile counters of the split-tile reduction sit kCounterStride 32-bit words (256 bytes) apart: every workgroup
 // publishes at the end of a launch, and device-scope atomics on one memory line are serialized (densely packed
 // counters cost the batch-1 GEMV on 8192 x 28672 layers 0.3-0.5 us).
@@ -150,6 +156,8 @@ struct Plan {
   bool reduce2;     // matrix-core kernel: split tiles reduced by a second kernel over the whole chip
   uint64_t ws_counters_off, ws_partials_off, ws_bytes;
   uint64_t ws_image_off;   // matrix-core kernel: activation images after the partial sums (0 for other kernels)
+  int mx_parts;            // > 0: the block-scaled matrix-core kernel (bpad batch rows, nt threads, rows rows per
+                           // workgroup), that many workgroups per row tile
   int kpt;                 // split-tile kernels: workgroups per tile with tile-aligned unit ranges (0: balanced split)
   int xv;                  // batch-1 and LUT batch kernels: kBigUnits for the instance staging that many units, else 0
 };
