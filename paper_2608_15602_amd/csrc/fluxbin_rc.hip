@@ -11,10 +11,14 @@
 // StructuralSearch (Def. Hessian-based Column Saliency, with a diagonal inverse Hessian): S_j = sum_i W_ij^2 / h_j^2,
 // and per block of g columns the s columns of largest saliency (equal scores: smaller column index first).
 //
-// Every step is a data-parallel kernel over the whole matrix (all blocks at once), launched in sequence on the stream.
+// Blocks of at most 128 columns (with eps > 0, and rows enough that the workspace holds the partial sums) run as fused
+// passes, one launch per base and round (below). Otherwise every step is a data-parallel kernel over the whole matrix (all
+// blocks at once). Launches are in sequence on the stream.
 // Sums use fixed reduction trees (no atomics), so results are deterministic. Arithmetic is fp64, the precision in which
 // the integer sign decisions are taken.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "fluxbin_internal.h"
 
@@ -195,20 +199,35 @@ __global__ void k_rc_bits(RcArgs a, uint32_t* out) {
   out[e] = bits;
 }
 
-// Column saliency S_j = sum_i W_ij^2 / h_j^2: a workgroup per 64 columns, four row slices combined in a fixed order.
-__global__ void __launch_bounds__(256) k_saliency(const float* W, const double* h, int64_t M, int64_t N, double* S) {
-  __shared__ double s_sum[4][64];
-  const int c = threadIdx.x & 63, slice = threadIdx.x >> 6;
-  const int64_t j = int64_t(blockIdx.x) * 64 + c;
+// Column saliency S_j = sum_i W_ij^2 / h_j^2: a 1024-thread workgroup per 16 columns, 64 row slices combined in a fixed
+// order. 16 columns (64-byte row segments) rather than 64: 4096 columns are then a workgroup per CU instead of 64 workgroups
+// of four row slices (4096 x 4096: 255 -> 22 us; a read of the matrix at 5 TB/s is 13 us).
+__global__ void __launch_bounds__(1024) k_saliency(const float* W, const double* h, int64_t M, int64_t N, double* S) {
+  __shared__ double s_sum[64][17];
+  const int c = threadIdx.x & 15, slice = threadIdx.x >> 4;
+  const int64_t j = int64_t(blockIdx.x) * 16 + c;
   double acc = 0.0;
-  if (j < N)
-    for (int64_t i = slice; i < M; i += 4) {
+  if (j < N) {
+    int64_t i = slice;
+    for (; i + 7 * 64 < M; i += 8 * 64) {   // eight loads in flight
+      float w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = W[(i + 64 * u) * N + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += double(w[u]) * double(w[u]);
+    }
+    for (; i < M; i += 64) {
       const double w = double(W[i * N + j]);
       acc += w * w;
     }
+  }
   s_sum[slice][c] = acc;
   __syncthreads();
-  if (slice == 0 && j < N) S[j] = (((s_sum[0][c] + s_sum[1][c]) + s_sum[2][c]) + s_sum[3][c]) / (h[j] * h[j]);
+  for (int half = 32; half >= 1; half >>= 1) {
+    if (slice < half) s_sum[slice][c] += s_sum[slice + half][c];
+    __syncthreads();
+  }
+  if (slice == 0 && j < N) S[j] = s_sum[0][c] / (h[j] * h[j]);
 }
 
 // Per block of g columns (a workgroup each, g <= 1024): column j is selected when fewer than s columns of the block
@@ -245,6 +264,651 @@ unsigned grid_for(int64_t n, int per) { return unsigned((n + per - 1) / per); }
 int64_t col_slices(int64_t M) {
   const int64_t s = M / 256;
   return s < 1 ? 1 : (s > 64 ? 64 : s);
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// Fused passes (blocks of at most 128 columns). One launch per base and round instead of five: a wavefront takes whole
+// rows of a block, so the joint sign search of the round before, base k's row scale and the row's terms of base k's
+// column sums follow one another on values in registers, and the matrix is read once per base and round. The column
+// scales need every row: a launch leaves one sum per row slice and column, and the next one's workgroups add the slices
+// of their block first. Signs are bits (one 64-bit word per row, block and 64 columns).
+//
+// With a mask (the salient columns of FluxBin-Hybrid: 8 or 16 of 128) only its columns are carried along: a wavefront's lanes
+// are the masked columns of several rows, and x (minus the prior bases) is computed once, into an fp64 copy of those columns.
+//
+// 4096 x 4096, 2 + 2 bases, 8 salient columns per block, 10 rounds, both decompositions and the saliency search:
+// 9880 -> 992 us. Of the 23 launches over the full matrix a round pass takes 25 us (64 MB of X: 13 us at the copy rate)
+// and one with the sign search about 50 (fp64 issue); a launch over the masked columns 9 to 12 us (latency).
+// ---------------------------------------------------------------------------------------------------------------------
+
+constexpr int kRcWaves = 8;        // wavefronts of a workgroup
+constexpr int kRcMaxG = 128;       // block columns: two per lane
+
+struct RcPass {
+  RcArgs a;
+  uint64_t* bits;          // [K][G][M][2] signs of a block's listed columns 0..63, 64..127 (set: +1)
+  const int32_t* nm;       // [G] listed columns of a block, or nullptr (all)
+  const uint16_t* cols;    // [G][g] their offsets in the block, increasing
+  const double* xc;        // x of the listed columns of blocks with nm <= cap: [M][nm] at blk * M * cap
+  int32_t cap;
+  int32_t kprev;           // base whose column sums num_in and den_in hold (-1: none)
+  int64_t rows_per_slice, slices;
+  const double* num_in;    // [slices][N], [slices][G]
+  const double* den_in;
+  double* num_out;
+  double* den_out;
+};
+
+// What a pass does with its rows, for base KB.
+enum RcMode {
+  kRcInit,       // greedy initialization: signs of the residual, then row scales and column sums
+  kRcRound,      // row scales and column sums with the signs as they are
+  kRcSignRound,  // the joint sign search first
+  kRcSign,       // the joint sign search only
+  kRcScales,     // no rows: only the column scales of the pass before
+};
+
+template <int CTRL>
+__device__ __forceinline__ double rc_dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = __builtin_amdgcn_mov_dpp(int(uint32_t(u)), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(int(uint32_t(u >> 32)), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, (uint64_t(uint32_t(hi)) << 32) | uint32_t(lo));
+}
+
+__device__ __forceinline__ double rc_readlane(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), lane));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), lane));
+  return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+}
+
+// Sums of four values over the wavefront, value lane & 3 in each lane: two exchange steps that halve the values carried,
+// then four that add over the lanes (3 + 4 additions instead of 24).
+__device__ __forceinline__ double rc_sum4(const double (&v)[4], int lane) {
+  const bool o1 = (lane & 1) != 0, o2 = (lane & 2) != 0;
+  const double a = (o1 ? v[1] : v[0]) + rc_dpp<0xB1>(o1 ? v[0] : v[1]);   // quad_perm 1,0,3,2
+  const double b = (o1 ? v[3] : v[2]) + rc_dpp<0xB1>(o1 ? v[2] : v[3]);
+  double s = (o2 ? b : a) + rc_dpp<0x4E>(o2 ? a : b);                       // quad_perm 2,3,0,1
+  s += rc_dpp<0x124>(s);                                                    // row_ror 4
+  s += rc_dpp<0x128>(s);                                                    // row_ror 8
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  return s;
+}
+
+// v with the sign of a +-1: negated where the mask's top bit is set.
+__device__ __forceinline__ double rc_flip(double v, uint32_t neg) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ (uint64_t(neg & 0x80000000u) << 32));
+}
+
+// Joint sign search (Prop. 3.3) for one element: the top bits of neg[k] are set where b_k = -1.
+template <int K>
+__device__ __forceinline__ void rc_search(double x, const double (&m)[K], uint32_t (&neg)[K]) {
+  double best = 0.0;
+  int best_c = 0;
+#pragma unroll
+  for (int c = 0; c < (1 << K); ++c) {
+    double approx = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) approx += ((c >> k) & 1) ? m[k] : -m[k];
+    const double err = fabs(x - approx);
+    if (c == 0 || err < best) {
+      best = err;
+      best_c = c;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) neg[k] = ((best_c >> k) & 1) ? 0u : 0x80000000u;
+}
+
+// Column scales of the lane's columns: base kprev's from the slices' sums (slice order), the others' as stored; base
+// k's are 1 in its initialization. col[c]: the lane's columns in the matrix, or -1.
+template <int K, int KB, RcMode MODE>
+__device__ __forceinline__ void rc_scales(const RcPass& p, int64_t blk, int64_t c0, int nc, const int64_t (&col)[2],
+                                          double* s_ac, double (&ac)[K][2]) {
+  const RcArgs& a = p.a;
+  if (p.kprev >= 0) {
+    const int t = int(threadIdx.x);
+    if (t < nc) {
+      double n = 0.0, d = 0.0;
+      for (int64_t r0 = 0; r0 < p.slices; r0 += 8) {
+        double u[8], w[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const bool in = r0 + r < p.slices;
+          u[r] = in ? p.num_in[(r0 + r) * a.N + c0 + t] : 0.0;
+          w[r] = in ? p.den_in[(r0 + r) * a.G + blk] : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          n += u[r];
+          d += w[r];
+        }
+      }
+      const bool in = p.nm == nullptr || rc_in(a, c0 + t);
+      const double v = in ? n / (d + a.eps) : 0.0;
+      s_ac[t] = v;
+      if (blockIdx.y == 0) a.ac[int64_t(p.kprev) * a.N + c0 + t] = v;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int kk = 0; kk < K; ++kk)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      double v = 0.0;
+      if (col[c] >= 0) {
+        if (MODE == kRcInit && kk == KB)
+          v = 1.0;
+        else if (kk == p.kprev)
+          v = s_ac[col[c] - c0];
+        else if (MODE != kRcInit || kk < KB)
+          v = a.ac[int64_t(kk) * a.N + col[c]];
+      }
+      ac[kk][c] = v;
+    }
+}
+
+// Target of base k for one element with the contributions m[kk] * b_kk of the other bases (order as rc_target).
+template <int K, int KB, RcMode MODE>
+__device__ __forceinline__ double rc_residual(double x, const double (&m)[K], const uint32_t (&neg)[K]) {
+  if constexpr (MODE == kRcInit) {
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk) x -= rc_flip(m[kk], neg[kk]);
+    return x;
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int kk = 0; kk < K; ++kk)
+    if (kk != KB) s += rc_flip(m[kk], neg[kk]);
+  return x - s;
+}
+
+// Whether a pass reads base kk's row scales / signs.
+template <int KB, RcMode MODE>
+__device__ __forceinline__ constexpr bool rc_reads_ar(int kk) {
+  return MODE == kRcInit ? kk < KB : MODE == kRcRound ? kk != KB : true;
+}
+template <int KB, RcMode MODE>
+__device__ __forceinline__ constexpr bool rc_reads_signs(int kk) {
+  return MODE == kRcInit ? kk < KB : MODE == kRcRound;
+}
+
+// The workgroup's column sums: the wavefronts' (and, with several rows per wavefront, the row groups') in a fixed order.
+__device__ __forceinline__ void rc_store_sums(const RcPass& p, int64_t blk, int64_t c0, int nc, const int (&off)[2],
+                                              const double (&cn)[2], double cd, double (&s_sum)[kRcWaves][kRcMaxG],
+                                              double (&s_den)[kRcWaves]) {
+  const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63;
+  __syncthreads();
+  for (int t = lane; t < nc; t += 64) s_sum[wave][t] = 0.0;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    if (off[c] >= 0) s_sum[wave][off[c]] = cn[c];
+  if (lane == 0) s_den[wave] = cd;
+  __syncthreads();
+  const int t = int(threadIdx.x);
+  if (t < nc) {
+    double n = 0.0;
+    for (int w = 0; w < kRcWaves; ++w) n += s_sum[w][t];
+    p.num_out[int64_t(blockIdx.y) * p.a.N + c0 + t] = n;
+  }
+  if (t == 0) {
+    double d = 0.0;
+    for (int w = 0; w < kRcWaves; ++w) d += s_den[w];
+    p.den_out[int64_t(blockIdx.y) * p.a.G + blk] = d;
+  }
+}
+
+// Four rows of a block as a wavefront loads them.
+template <int K>
+struct RcRows {
+  float x[4][2];
+  double ar[K][4];
+  uint32_t w[K][4][2];
+};
+
+// Every column of the block, X as given: lane l has columns l and l + 64, a wavefront four rows at a time, the next four
+// requested before them.
+template <int K, int KB, RcMode MODE>
+__global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
+  __shared__ double s_ac[kRcMaxG], s_sum[kRcWaves][kRcMaxG], s_den[kRcWaves];
+  constexpr bool kUpdate = MODE != kRcSign, kSearch = MODE == kRcSign || MODE == kRcSignRound;
+  const RcArgs& a = p.a;
+  const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int64_t blk = blockIdx.x, c0 = blk * a.g;
+  const int nc = int(c0 + a.g < a.N ? a.g : a.N - c0);
+  const int off[2] = {lane < nc ? lane : -1, lane + 64 < nc ? lane + 64 : -1};
+  const int64_t col[2] = {off[0] >= 0 ? c0 + off[0] : -1, off[1] >= 0 ? c0 + off[1] : -1};
+  const int64_t i0 = int64_t(blockIdx.y) * p.rows_per_slice;
+  const int64_t i1 = i0 + p.rows_per_slice < a.M ? i0 + p.rows_per_slice : a.M;
+  const float* xp = a.X + c0;
+  // columns past the block read its first one; their scales are zero and their x is replaced by zero
+  const int offc[2] = {off[0] >= 0 ? off[0] : 0, off[1] >= 0 ? off[1] : 0};
+  auto load = [&](int64_t i, RcRows<K>& r) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t row = i + u < i1 ? i + u : i1 - 1;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) r.x[u][c] = xp[row * a.N + offc[c]];
+#pragma unroll
+      for (int kk = 0; kk < K; ++kk) {
+        if (rc_reads_ar<KB, MODE>(kk)) r.ar[kk][u] = a.ar[(int64_t(kk) * a.M + row) * a.G + blk];
+        if (rc_reads_signs<KB, MODE>(kk)) {
+          const uint32_t* q = reinterpret_cast<const uint32_t*>(p.bits + ((int64_t(kk) * a.G + blk) * a.M + row) * 2);
+          r.w[kk][u][0] = q[lane >> 5];
+          r.w[kk][u][1] = q[2 + (lane >> 5)];
+        }
+      }
+    }
+  };
+  int64_t i = i0 + 4 * wave;
+  RcRows<K> next;
+  if (i < i1) load(i, next);   // while the column scales are put together
+  double ac[K][2];
+  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, ac);
+  const double den = kUpdate ? wave_sum(ac[KB][0] * ac[KB][0] + ac[KB][1] * ac[KB][1]) + a.eps : 0.0;
+
+  double cn[2] = {0.0, 0.0}, cd = 0.0;
+  for (; i < i1; i += 4 * kRcWaves) {
+    const RcRows<K> r = next;
+    if (i + 4 * kRcWaves < i1) load(i + 4 * kRcWaves, next);
+    asm volatile("" ::: "memory");   // requested here
+    double num[4], tgt[4][2];
+    uint32_t neg[4][2];   // base KB's signs
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      num[u] = 0.0;
+      uint64_t ball[K][2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const double x = off[c] >= 0 ? double(r.x[u][c]) : 0.0;
+        double m[K];
+        uint32_t ng[K];
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+          m[kk] = rc_reads_ar<KB, MODE>(kk) ? r.ar[kk][u] * ac[kk][c] : 0.0;
+          ng[kk] = rc_reads_signs<KB, MODE>(kk) ? ~(r.w[kk][u][c] << (31 - (lane & 31))) : 0u;
+        }
+        if constexpr (kSearch) {
+          rc_search<K>(x, m, ng);
+#pragma unroll
+          for (int kk = 0; kk < K; ++kk)
+            ball[kk][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && (ng[kk] >> 31) == 0);
+        }
+        if constexpr (kUpdate) {
+          tgt[u][c] = rc_residual<K, KB, MODE>(x, m, ng);
+          neg[u][c] = ng[KB];
+          if constexpr (MODE == kRcInit) {
+            neg[u][c] = tgt[u][c] >= 0.0 ? 0u : 0x80000000u;
+            ball[KB][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && neg[u][c] == 0u);
+          }
+          num[u] += rc_flip(ac[KB][c], neg[u][c]) * tgt[u][c];
+        }
+      }
+      if ((kSearch || MODE == kRcInit) && i + u < i1 && lane < 2) {
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk)
+          if (kSearch || kk == KB)
+            p.bits[((int64_t(kk) * a.G + blk) * a.M + i + u) * 2 + lane] = lane == 0 ? ball[kk][0] : ball[kk][1];
+      }
+    }
+    if constexpr (kUpdate) {
+      const double v = rc_sum4(num, lane) / den;
+      if (lane < 4 && i + lane < i1) a.ar[(int64_t(KB) * a.M + i + lane) * a.G + blk] = v;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i + u >= i1) continue;
+        const double vu = rc_readlane(v, u);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) cn[c] += rc_flip(vu, neg[u][c]) * tgt[u][c];
+        cd += vu * vu;
+      }
+    }
+  }
+  if constexpr (kUpdate) rc_store_sums(p, blk, c0, nc, off, cn, cd, s_sum, s_den);
+}
+
+// Listed columns only (and prior bases): U groups of 64 / P rows at a time, P = 8, 16, 32 or 64 lanes per row, C = 2
+// columns per lane where a block lists more than 64. Bound by latency (loads, exchanges, a quotient per row), so the
+// groups' loads are requested together.
+template <int K, int KB, RcMode MODE, int U, int C>
+__device__ __forceinline__ void rc_list_rows(const RcPass& p, int64_t blk, int nm, int P, const int (&off)[2],
+                                             const int64_t (&col)[2], const double (&ac)[K][2], double den,
+                                             double (&cn)[2], double& cd) {
+  constexpr bool kUpdate = MODE != kRcSign, kSearch = MODE == kRcSign || MODE == kRcSignRound;
+  const RcArgs& a = p.a;
+  const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int RW = 64 / P, pos = lane & (P - 1), sub = lane / P;
+  const int64_t i0 = int64_t(blockIdx.y) * p.rows_per_slice;
+  const int64_t i1 = i0 + p.rows_per_slice < a.M ? i0 + p.rows_per_slice : a.M;
+  const bool copied = p.xc != nullptr && nm <= p.cap;
+  const int64_t base_words = a.G * a.M * 2;
+  for (int64_t ib = i0 + U * RW * wave; ib < i1; ib += U * RW * kRcWaves) {
+    double x[U][C], ar[K][U];
+    uint64_t w[K][U][C];
+    int64_t row[U];
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = ib + RW * u + sub;
+      in[u] = i < i1;
+      row[u] = in[u] ? i : i1 - 1;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        x[u][c] = 0.0;
+        if (off[c] >= 0)
+          x[u][c] = copied ? p.xc[blk * a.M * p.cap + row[u] * nm + pos + 64 * c] : rc_x(a, row[u], col[c]);
+      }
+#pragma unroll
+      for (int kk = 0; kk < K; ++kk) {
+        if (rc_reads_ar<KB, MODE>(kk)) ar[kk][u] = a.ar[(int64_t(kk) * a.M + row[u]) * a.G + blk];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (rc_reads_signs<KB, MODE>(kk)) w[kk][u][c] = p.bits[kk * base_words + (blk * a.M + row[u]) * 2 + c];
+      }
+    }
+    double num[U], tgt[U][C];
+    uint32_t neg[U][C];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      num[u] = 0.0;
+      uint64_t* word = p.bits + (blk * a.M + row[u]) * 2;
+      auto store = [&](int kk, int c, bool plus) __attribute__((always_inline)) {
+        const uint64_t ball = __builtin_amdgcn_ballot_w64(off[c] >= 0 && plus);
+        if (in[u] && pos == 0)
+          word[kk * base_words + c] = P == 64 ? ball : (ball >> (sub * P)) & ((uint64_t(1) << P) - 1);
+      };
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        double m[K];
+        uint32_t ng[K];
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+          m[kk] = rc_reads_ar<KB, MODE>(kk) ? ar[kk][u] * ac[kk][c] : 0.0;
+          ng[kk] = rc_reads_signs<KB, MODE>(kk) ? (((w[kk][u][c] >> pos) & 1u) != 0 ? 0u : 0x80000000u) : 0u;
+        }
+        if constexpr (kSearch) {
+          rc_search<K>(x[u][c], m, ng);
+#pragma unroll
+          for (int kk = 0; kk < K; ++kk) store(kk, c, ng[kk] == 0u);
+        }
+        if constexpr (kUpdate) {
+          tgt[u][c] = rc_residual<K, KB, MODE>(x[u][c], m, ng);
+          neg[u][c] = ng[KB];
+          if constexpr (MODE == kRcInit) {
+            neg[u][c] = tgt[u][c] >= 0.0 ? 0u : 0x80000000u;
+            store(KB, c, neg[u][c] == 0u);
+          }
+          num[u] += rc_flip(ac[KB][c], neg[u][c]) * tgt[u][c];
+        }
+      }
+    }
+    if constexpr (kUpdate) {
+      for (int s = 1; s < P; s <<= 1)
+#pragma unroll
+        for (int u = 0; u < U; ++u) num[u] += __shfl_xor(num[u], s, 64);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double r = num[u] / den;
+        if (!in[u]) continue;
+        if (pos == 0) a.ar[(int64_t(KB) * a.M + row[u]) * a.G + blk] = r;
+#pragma unroll
+        for (int c = 0; c < C; ++c) cn[c] += rc_flip(r, neg[u][c]) * tgt[u][c];
+        cd += r * r;
+      }
+    }
+  }
+}
+
+template <int K, int KB, RcMode MODE>
+__global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass_list(RcPass p) {
+  __shared__ double s_ac[kRcMaxG], s_sum[kRcWaves][kRcMaxG], s_den[kRcWaves];
+  constexpr bool kUpdate = MODE != kRcSign;
+  const RcArgs& a = p.a;
+  const int lane = int(threadIdx.x) & 63;
+  const int64_t blk = blockIdx.x, c0 = blk * a.g;
+  const int nc = int(c0 + a.g < a.N ? a.g : a.N - c0);
+  const int nm = p.nm != nullptr ? p.nm[blk] : nc;
+  const int P = nm > 32 ? 64 : nm > 16 ? 32 : nm > 8 ? 16 : 8;
+  const int pos = lane & (P - 1);
+  int off[2];
+  int64_t col[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int e = pos + 64 * c;
+    off[c] = (c == 0 || P == 64) && e < nm ? (p.nm != nullptr ? int(p.cols[blk * a.g + e]) : e) : -1;
+    col[c] = off[c] >= 0 ? c0 + off[c] : -1;
+  }
+  double ac[K][2];
+  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, ac);
+  double den = ac[KB][0] * ac[KB][0] + ac[KB][1] * ac[KB][1];
+  for (int s = 1; s < P; s <<= 1) den += __shfl_xor(den, s, 64);
+  den += a.eps;
+
+  double cn[2] = {0.0, 0.0}, cd = 0.0;
+  if (nm > 64)
+    rc_list_rows<K, KB, MODE, 1, 2>(p, blk, nm, P, off, col, ac, den, cn, cd);
+  else
+    rc_list_rows<K, KB, MODE, 4, 1>(p, blk, nm, P, off, col, ac, den, cn, cd);
+  if constexpr (kUpdate) {
+    for (int s = P; s < 64; s <<= 1) {   // the wavefront's row groups
+      cn[0] += __shfl_xor(cn[0], s, 64);
+      cd += __shfl_xor(cd, s, 64);
+    }
+    if (lane >= P) off[0] = off[1] = -1;
+    rc_store_sums(p, blk, c0, nc, off, cn, cd, s_sum, s_den);
+  }
+}
+
+// Only the column scales of the pass before.
+template <int K>
+__global__ void __launch_bounds__(64 * kRcWaves) k_rc_last_scales(RcPass p) {
+  __shared__ double s_ac[kRcMaxG];
+  const int64_t blk = blockIdx.x, c0 = blk * p.a.g, none[2] = {-1, -1};
+  double ac[K][2];
+  rc_scales<K, 0, kRcScales>(p, blk, c0, int(c0 + p.a.g < p.a.N ? p.a.g : p.a.N - c0), none, s_ac, ac);
+}
+
+// The masked columns of every block (a workgroup each): their offsets, their number, and zero column scales off the mask.
+__global__ void __launch_bounds__(kRcMaxG) k_rc_list(RcArgs a, int32_t* nm, uint16_t* cols, uint16_t* pos) {
+  __shared__ int in[kRcMaxG];
+  const int t = int(threadIdx.x);
+  const int64_t c0 = int64_t(blockIdx.x) * a.g;
+  const int nc = int(c0 + a.g < a.N ? a.g : a.N - c0);
+  in[t] = t < nc && rc_in(a, c0 + t) ? 1 : 0;
+  __syncthreads();
+  int before = 0;
+  for (int u = 0; u < t; ++u) before += in[u];
+  if (t < nc) {
+    pos[c0 + t] = in[t] != 0 ? uint16_t(before) : uint16_t(0xFFFFu);
+    if (in[t] != 0)
+      cols[int64_t(blockIdx.x) * a.g + before] = uint16_t(t);
+    else
+      for (int k = 0; k < a.K; ++k) a.ac[int64_t(k) * a.N + c0 + t] = 0.0;
+  }
+  if (t == kRcMaxG - 1) nm[blockIdx.x] = before + in[t];
+}
+
+// x of the listed columns [M][nm] of the blocks that list at most cap.
+__global__ void __launch_bounds__(256) k_rc_copy(RcArgs a, const int32_t* nm, const uint16_t* cols, int cap, double* xc) {
+  const int64_t blk = blockIdx.y;
+  const int n = nm[blk];
+  if (n > cap) return;
+  for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < a.M * n; e += int64_t(gridDim.x) * 256) {
+    const int64_t i = e / n;
+    xc[blk * a.M * cap + e] = rc_x(a, i, blk * a.g + cols[blk * a.g + (e - i * n)]);
+  }
+}
+
+// The blocks' sign words to canonical planes [K][M][ceil(N/32)], blocks of whole words: one thread per (base, block, row).
+__global__ void __launch_bounds__(256) k_rc_planes_blocks(RcArgs a, const uint64_t* bits, const int32_t* nm,
+                                                          const uint16_t* cols, uint32_t* out) {
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x, blk = blockIdx.y, k = blockIdx.z;
+  if (i >= a.M) return;
+  const int64_t W = (a.N + 31) / 32, w0 = blk * (a.g / 32);
+  uint64_t v[2] = {bits[((k * a.G + blk) * a.M + i) * 2], bits[((k * a.G + blk) * a.M + i) * 2 + 1]};
+  if (nm != nullptr) {   // listed columns to their places
+    uint64_t to[2] = {0, 0};
+    const int n = nm[blk];
+    for (int e = 0; e < n; ++e) {
+      const int t = cols[blk * a.g + e];
+      const uint64_t bit = ((e < 64 ? v[0] : v[1]) >> (e & 63)) & 1u;
+      to[0] |= t < 64 ? bit << t : 0;
+      to[1] |= t >= 64 ? bit << (t & 63) : 0;
+    }
+    v[0] = to[0];
+    v[1] = to[1];
+  }
+  uint32_t* dst = out + (k * a.M + i) * W + w0;
+  for (int w = 0; w < a.g / 32 && w0 + w < W; ++w) dst[w] = uint32_t(v[w >> 1] >> (32 * (w & 1)));
+}
+
+// The same for any block width: one thread per word.
+__global__ void __launch_bounds__(256) k_rc_planes(RcArgs a, const uint64_t* bits, const uint16_t* pos, uint32_t* out) {
+  const int64_t W = (a.N + 31) / 32;
+  const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (e >= int64_t(a.K) * a.M * W) return;
+  const int64_t row = e / W, w = e - row * W, k = row / a.M, i = row - k * a.M;
+  uint32_t v = 0u;
+  for (int t = 0; t < 32; ++t) {
+    const int64_t j = w * 32 + t;
+    if (j >= a.N) break;
+    const int64_t blk = j / a.g;
+    const int q = pos != nullptr ? int(pos[j]) : int(j - blk * a.g);
+    if (q == 0xFFFF) continue;
+    v |= uint32_t((bits[((k * a.G + blk) * a.M + i) * 2 + (q >> 6)] >> (q & 63)) & 1u) << t;
+  }
+  out[e] = v;
+}
+
+// Workspace of the fused passes within `bytes`; false if they do not fit (few rows) or do not take the call.
+struct RcPlan {
+  size_t bits, num[2], den[2], nm, cols, pos, xc;
+  int64_t slices, rows_per_slice;
+  int32_t cap;
+};
+
+bool rc_plan(const RcArgs& a, size_t bytes, RcPlan* q) {
+  // eps = 0: the quotients off the mask are 0 / 0 in the general kernels
+  if (a.g > kRcMaxG || !(a.eps > 0.0) || a.M >= (int64_t(1) << 31) || a.G > 65535) return false;
+  // about two workgroups per CU, at least 64 rows each (two rounds of the wavefronts)
+  int64_t s = (512 + a.G - 1) / a.G;
+  const int64_t most = (a.M + 63) / 64;
+  s = s < 1 ? 1 : s > 64 ? 64 : s;
+  s = s > most ? most : s;
+  q->rows_per_slice = ((a.M + s - 1) / s + 31) / 32 * 32;
+  q->slices = (a.M + q->rows_per_slice - 1) / q->rows_per_slice;
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    const size_t at = off;
+    off = (off + n + 255) & ~size_t(255);
+    return at;
+  };
+  q->bits = take(size_t(a.K) * size_t(a.G) * size_t(a.M) * 16);
+  for (int i = 0; i < 2; ++i) {
+    q->num[i] = take(size_t(q->slices) * size_t(a.N) * 8);
+    q->den[i] = take(size_t(q->slices) * size_t(a.G) * 8);
+  }
+  q->nm = q->cols = q->pos = q->xc = 0;
+  q->cap = 0;
+  if (a.mask != nullptr) {
+    q->nm = take(size_t(a.G) * 4);
+    q->cols = take(size_t(a.G) * size_t(a.g) * 2);
+    q->pos = take(size_t(a.N) * 2);
+    if (off < bytes) {   // the rest: fp64 copies of up to cap columns of every block
+      const size_t per = size_t(a.G) * size_t(a.M) * 8;
+      const size_t c = (bytes - off) / per;
+      q->cap = int32_t(c > 64 ? 64 : c);
+      q->xc = off;
+    }
+  }
+  return off <= bytes;
+}
+
+template <int K, int KB, RcMode MODE>
+void rc_launch(const RcPass& p, bool list, hipStream_t stream) {
+  const dim3 grid(unsigned(p.a.G), unsigned(p.slices)), block(64 * kRcWaves);
+  if (list)
+    hipLaunchKernelGGL((k_rc_pass_list<K, KB, MODE>), grid, block, 0, stream, p);
+  else
+    hipLaunchKernelGGL((k_rc_pass<K, KB, MODE>), grid, block, 0, stream, p);
+}
+
+template <int K>
+void rc_fused(const RcArgs& a, const RcPlan& q, int T, uint8_t* ws, uint32_t* d_signs, hipStream_t stream) {
+  RcPass p{};
+  p.a = a;
+  p.bits = reinterpret_cast<uint64_t*>(ws + q.bits);
+  p.rows_per_slice = q.rows_per_slice;
+  p.slices = q.slices;
+  const bool masked = a.mask != nullptr, list = masked || a.pB != nullptr;
+  int32_t* nm = reinterpret_cast<int32_t*>(ws + q.nm);
+  uint16_t* cols = reinterpret_cast<uint16_t*>(ws + q.cols);
+  uint16_t* pos = reinterpret_cast<uint16_t*>(ws + q.pos);
+  if (masked) {
+    p.nm = nm;
+    p.cols = cols;
+    hipLaunchKernelGGL(k_rc_list, dim3(unsigned(a.G)), dim3(kRcMaxG), 0, stream, a, nm, cols, pos);
+    if (q.cap > 0) {
+      double* xc = reinterpret_cast<double*>(ws + q.xc);
+      p.xc = xc;
+      p.cap = q.cap;
+      hipLaunchKernelGGL(k_rc_copy, dim3(grid_for(a.M * 8, 256), unsigned(a.G)), dim3(256), 0, stream, a, nm, cols, q.cap,
+                         xc);
+    }
+  }
+  int turn = 0;
+  auto buffers = [&](int kprev) {
+    p.kprev = kprev;
+    p.num_in = reinterpret_cast<double*>(ws + q.num[turn]);
+    p.den_in = reinterpret_cast<double*>(ws + q.den[turn]);
+    turn ^= 1;
+    p.num_out = reinterpret_cast<double*>(ws + q.num[turn]);
+    p.den_out = reinterpret_cast<double*>(ws + q.den[turn]);
+  };
+  auto init = [&](auto kb) {
+    constexpr int KB = decltype(kb)::value;
+    if constexpr (KB < K) {
+      buffers(KB - 1);
+      rc_launch<K, KB, kRcInit>(p, list, stream);
+    }
+  };
+  auto round = [&](auto kb) {
+    constexpr int KB = decltype(kb)::value;
+    if constexpr (KB < K) {
+      buffers(KB == 0 ? K - 1 : KB - 1);
+      rc_launch<K, KB, kRcRound>(p, list, stream);
+    }
+  };
+  using std::integral_constant;
+  init(integral_constant<int, 0>());
+  init(integral_constant<int, 1>());
+  init(integral_constant<int, 2>());
+  init(integral_constant<int, 3>());
+  for (int t = 0; t < T; ++t) {
+    if (t == 0) {
+      round(integral_constant<int, 0>());
+    } else {
+      buffers(K - 1);
+      rc_launch<K, 0, kRcSignRound>(p, list, stream);
+    }
+    round(integral_constant<int, 1>());
+    round(integral_constant<int, 2>());
+    round(integral_constant<int, 3>());
+  }
+  buffers(K - 1);   // the last column scales, and the last round's signs
+  if (T > 0)
+    rc_launch<K, 0, kRcSign>(p, list, stream);
+  else
+    hipLaunchKernelGGL(k_rc_last_scales<K>, dim3(unsigned(a.G)), dim3(64 * kRcWaves), 0, stream, p);
+  if (a.g % 32 == 0)
+    hipLaunchKernelGGL(k_rc_planes_blocks, dim3(grid_for(a.M, 256), unsigned(a.G), unsigned(K)), dim3(256), 0, stream, a,
+                       p.bits, p.nm, p.cols, d_signs);
+  else
+    hipLaunchKernelGGL(k_rc_planes, dim3(grid_for(int64_t(K) * a.M * ((a.N + 31) / 32), 256)), dim3(256), 0, stream, a,
+                       p.bits, masked ? pos : nullptr, d_signs);
 }
 
 }  // namespace
@@ -300,6 +964,19 @@ fluxbin_status fluxbin_rc_decompose(const float* d_X, const uint8_t* d_mask, con
   a.pg = d_prior_signs ? gp : 1;
   a.pG = (N + a.pg - 1) / a.pg;
   a.pW = (N + 31) / 32;
+  RcPlan plan;
+  if (rc_plan(a, need, &plan)) {   // by the queried size: the same kernels for any larger workspace
+    uint8_t* ws = static_cast<uint8_t*>(d_ws);
+    switch (K) {
+      case 1: rc_fused<1>(a, plan, T, ws, d_signs, stream); break;
+      case 2: rc_fused<2>(a, plan, T, ws, d_signs, stream); break;
+      case 3: rc_fused<3>(a, plan, T, ws, d_signs, stream); break;
+      default: rc_fused<4>(a, plan, T, ws, d_signs, stream); break;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "launching the decomposition kernels");
+    return FLUXBIN_OK;
+  }
   const int64_t elems = M * N;
   const int64_t slices = col_slices(M);
   const int64_t rows_per_slice = (M + slices - 1) / slices;
@@ -342,7 +1019,7 @@ fluxbin_status fluxbin_structural_search(const float* d_W, const double* d_hinv_
   if (g > 1024) return fail(FLUXBIN_ERR_UNSUPPORTED, "group of %lld columns > 1024", (long long)g);
   if (s > g) return fail(FLUXBIN_ERR_INVALID_ARG, "s = %lld > g = %lld", (long long)s, (long long)g);
   if (M * N > (int64_t(1) << 36)) return fail(FLUXBIN_ERR_UNSUPPORTED, "matrix too large");
-  hipLaunchKernelGGL(k_saliency, dim3(grid_for(N, 64)), dim3(256), 0, stream, d_W, d_hinv_diag, M, N, d_scores);
+  hipLaunchKernelGGL(k_saliency, dim3(grid_for(N, 16)), dim3(1024), 0, stream, d_W, d_hinv_diag, M, N, d_scores);
   hipLaunchKernelGGL(k_topk, dim3(unsigned((N + g - 1) / g)), dim3(1024), 0, stream, d_scores, N, g, s, d_sal_idx,
                      d_mask);
   hipError_t e = hipGetLastError();
