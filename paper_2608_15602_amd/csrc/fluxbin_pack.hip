@@ -75,110 +75,149 @@ __device__ inline int pos_of(int u, int64_t i, int spc, int G) {
   return blk * n + w;
 }
 
-// The 128 virtual sign bits of chunk c for row i (bit r of the result <-> virtual column 128 c + r).
-__device__ inline void chunk_bits(const PackArgs& a, int64_t c, int64_t i, uint32_t out[4]) {
-  out[0] = out[1] = out[2] = out[3] = 0u;
-  if (i >= a.M) return;
-  int64_t k, col0;
-  const int kind = chunk_kind(a, c, &k, &col0);
-  if (kind == 0) {
-    const uint32_t* row = a.signs + (k * a.M + i) * a.W;
-    for (int m = 0; m < 4; ++m) {
-      const int64_t j0 = col0 + 32 * m;
-      if (j0 >= a.N) break;
-      uint32_t word = row[j0 / 32];
-      const int64_t valid = a.N - j0;
-      if (valid < 32) word &= (1u << valid) - 1u;
-      out[m] = word;
-    }
-  } else if (kind == 1) {
-    const uint32_t* row = a.sal_signs + (k * a.M + i) * a.W;
-    for (int r = 0; r < kChunk; ++r) {
-      const int64_t t = col0 + r;
-      if (t >= a.S) break;
-      const int64_t j = a.sal_idx[t];
-      const uint32_t bit = (row[j >> 5] >> (j & 31)) & 1u;
-      out[r >> 5] |= bit << (r & 31);
-    }
-  }
+// 128 bits rotated right by rot: bit b of the result is bit (b + rot) mod 128.
+__device__ inline void rotate_right(uint32_t w[4], uint32_t rot) {
+  const uint32_t sb = rot & 31u;
+  uint32_t f[4];
+  for (int m = 0; m < 4; ++m) f[m] = __builtin_amdgcn_alignbit(w[(m + 1) & 3], w[m], sb);
+  const bool r1 = (rot & 32u) != 0, r2 = (rot & 64u) != 0;
+  uint32_t h[4];
+  for (int m = 0; m < 4; ++m) h[m] = r1 ? f[(m + 1) & 3] : f[m];
+  for (int m = 0; m < 4; ++m) w[m] = r2 ? h[(m + 2) & 3] : h[m];
 }
 
-// One thread per 16-byte entry (super-chunk sc, slot h, row i < Mp).
-__global__ void k_pack_signs(PackArgs a) {
-  const int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  const int64_t n = a.NSC * 2 * a.Mp;
-  if (e >= n) return;
-  const int64_t i = e % a.Mp;
-  const int64_t sh = e / a.Mp;
-  const int64_t sc = sh >> 1;
-  const int64_t h = sh & 1;
-  uint32_t bits[4];
-  uint32_t o[4] = {0u, 0u, 0u, 0u};
-  if (a.mu == 8) {
-    const int64_t c = 2 * sc + (h ^ ((i & 31) >= 16 ? 1 : 0));
-    chunk_bits(a, c, i, bits);
-    const int G = int(chunk_G(a, c));
-    for (int q = 0; q < 16; ++q) {
-      const int u = sub_at(q, i, 16, G);
-      const uint32_t byte = (bits[u >> 2] >> (8 * (u & 3))) & 0xFFu;
-      o[q >> 2] |= byte << (8 * (q & 3));
-    }
-  } else {
-    const int64_t c = 2 * sc + h;
-    chunk_bits(a, c, i, bits);
-    const int G = int(chunk_G(a, c));
-    for (int q = 0; q < 32; ++q) {
-      const int u = sub_at(q, i, 32, G);
-      const uint32_t nib = (bits[u >> 3] >> (4 * (u & 7))) & 0xFu;
-      o[q >> 3] |= nib << (4 * (q & 7));
-    }
-  }
-  uint4* dst = reinterpret_cast<uint4*>(a.base + a.off_signs) + e;
-  *dst = make_uint4(o[0], o[1], o[2], o[3]);
-}
+constexpr int kPackRows = 64, kPackChunks = 16;   // a workgroup's tile of packed entries
 
-// One thread per (row-scale plane, row < Mp). Coarse planes hold one scale per row; a fine chunk's block of G planes
-// holds, for each row, G consecutive scales: slot b is the scale of the chunk's group (b + floor(i/n)) mod G (n = spc/G
-// sub-vectors per group), i.e. the group read at positions b*n .. b*n+n-1 of the row's rotated entry.
-__global__ void k_pack_rscale(PackArgs a) {
-  const int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (e >= a.NRP * a.Mp) return;
-  const bool salient = e >= a.Pg * a.Mp;
-  const int64_t G = salient ? a.Gcs : a.Gcg;
-  const int64_t e2 = salient ? e - a.Pg * a.Mp : e;
-  uint16_t v = 0;
-  if (G == 1) {
-    const int64_t i = e2 % a.Mp;
-    const int64_t plane = e2 / a.Mp;
-    if (i < a.M) {
-      if (!salient) {
-        const int64_t k = plane / a.Gr, g = plane % a.Gr;
-        v = a.alpha_r[(k * a.M + i) * a.Gr + g];
-      } else {
-        const int64_t k = plane / a.Gs, g = plane % a.Gs;
-        v = a.alpha_sr[(k * a.M + i) * a.Gs + g];
+// A workgroup packs 64 rows x 16 chunks: a transpose of 16-byte pieces through LDS. A wavefront reads 256 contiguous bytes
+// of a row (the tile's 16 chunks of a global base, one word per lane) and writes 1 KB runs of a chunk's rows. A salient
+// chunk's bits are gathered 64 columns at a time, a lane each, and collected by a ballot: the column indices are read
+// once per tile and the row's words come from the caches. Bound by memory: 28672 x 8192 with 3 bases + 5% (117 MB read,
+// 90 MB written) 229 -> 58 us; one thread per entry read rows 1 KB apart and salient columns one after another.
+__global__ void __launch_bounds__(256) k_pack_signs(PackArgs a) {
+  __shared__ uint32_t tile[kPackRows][4 * kPackChunks + 4];   // 4 words of padding: rows on different banks
+  const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
+  // the last chunks first: the salient ones, whose workgroups take longest
+  const int64_t i0 = int64_t(blockIdx.x) * kPackRows, c0 = int64_t(gridDim.y - 1 - blockIdx.y) * kPackChunks;
+  {
+    // global chunks: lane l takes word l & 3 of chunk c0 + l / 4
+    const int64_t c = c0 + (lane >> 2);
+    int64_t k = 0, col0 = 0;
+    const bool global = c < a.NCP && chunk_kind(a, c, &k, &col0) == 0;
+    const int64_t j0 = col0 + 32 * (lane & 3);
+    const bool read = global && j0 < a.N;
+    const uint32_t keep = a.N - j0 < 32 ? (1u << ((a.N - j0) & 31)) - 1u : ~0u;
+    const uint32_t* src = a.signs + (read ? k * a.M * a.W + j0 / 32 : 0);
+    uint32_t w[kPackRows / 4];
+#pragma unroll
+    for (int r = 0; r < kPackRows / 4; ++r) {
+      const int64_t i = i0 + 4 * r + wave;
+      w[r] = read && i < a.M ? src[i * a.W] & keep : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kPackRows / 4; ++r) tile[4 * r + wave][lane] = w[r];
+  }
+  __syncthreads();
+  const int64_t cs = a.ngcp > c0 ? a.ngcp : c0;
+  const int64_t ce = c0 + kPackChunks < a.NC ? c0 + kPackChunks : a.NC;
+  for (int64_t c = cs; c < ce; ++c) {   // salient chunks of the tile
+    int64_t k, col0;
+    if (chunk_kind(a, c, &k, &col0) != 1) continue;
+    for (int half = 0; half < 2; ++half) {
+      const int64_t t = col0 + 64 * half + lane;
+      const bool in = t < a.S;
+      const int32_t j = in ? a.sal_idx[t] : 0;
+      const uint32_t* src = a.sal_signs + k * a.M * a.W + (j >> 5);
+      uint32_t w[kPackRows / 4];
+#pragma unroll
+      for (int r = 0; r < kPackRows / 4; ++r) {
+        const int64_t i = i0 + 4 * r + wave;
+        w[r] = in && i < a.M ? src[i * a.W] : 0u;
+      }
+#pragma unroll
+      for (int r = 0; r < kPackRows / 4; ++r) {
+        const uint64_t bits = __builtin_amdgcn_ballot_w64(((w[r] >> (j & 31)) & 1u) != 0);
+        if (lane < 2) tile[4 * r + wave][4 * (c - c0) + 2 * half + lane] = uint32_t(bits >> (32 * lane));
       }
     }
-  } else {
-    const int64_t blk = e2 / (a.Mp * G);                 // (base, chunk within the base)
-    const int64_t i = (e2 % (a.Mp * G)) / G;
-    const int64_t b = e2 % G;
-    const int64_t nc = salient ? a.ncs : a.ncg;
-    const int64_t k = blk / nc, lc = blk % nc;
-    const int64_t n = (kChunk / a.mu) / G;
-    const int64_t grp = lc * G + (b + i / n) % G;
-    if (i < a.M) {
-      if (!salient && grp < a.Gr) v = a.alpha_r[(k * a.M + i) * a.Gr + grp];
-      if (salient && grp < a.Gs) v = a.alpha_sr[(k * a.M + i) * a.Gs + grp];
-    }
   }
-  reinterpret_cast<uint16_t*>(a.base + a.off_rscale)[e] = v;
+  __syncthreads();
+  const int64_t i = i0 + lane;   // Mp is a multiple of 64: every row of the tile is written
+  for (int q = wave; q < kPackChunks && c0 + q < a.NCP; q += 4) {
+    const int64_t c = c0 + q;
+    uint32_t bits[4];
+    for (int m = 0; m < 4; ++m) bits[m] = tile[lane][4 * q + m];
+    const int G = int(chunk_G(a, c));
+    if (G == 1 || G == kChunk / a.mu) {
+      rotate_right(bits, uint32_t(a.mu * i) & 127u);
+    } else {
+      uint32_t o[4] = {0u, 0u, 0u, 0u};
+      if (a.mu == 8) {
+        for (int p = 0; p < 16; ++p) {
+          const int u = sub_at(p, i, 16, G);
+          o[p >> 2] |= ((bits[u >> 2] >> (8 * (u & 3))) & 0xFFu) << (8 * (p & 3));
+        }
+      } else {
+        for (int p = 0; p < 32; ++p) {
+          const int u = sub_at(p, i, 32, G);
+          o[p >> 3] |= ((bits[u >> 3] >> (4 * (u & 7))) & 0xFu) << (4 * (p & 7));
+        }
+      }
+      for (int m = 0; m < 4; ++m) bits[m] = o[m];
+    }
+    const int64_t h = a.mu == 8 ? (c & 1) ^ ((i & 31) >= 16 ? 1 : 0) : (c & 1);
+    reinterpret_cast<uint4*>(a.base + a.off_signs)[((c & ~int64_t(1)) + h) * a.Mp + i] =
+        make_uint4(bits[0], bits[1], bits[2], bits[3]);
+  }
+}
+
+// Coarse row scales, a transpose of 64 rows x up to 64 groups through LDS: src [K][M][groups] -> planes [K * groups][Mp]
+// from plane p0 (rows past M zero). The tile's source is read in memory order.
+__global__ void __launch_bounds__(256) k_pack_rscale_planes(PackArgs a, const uint16_t* src, int64_t groups, int64_t p0) {
+  __shared__ uint16_t tile[64][65];
+  const int64_t i0 = int64_t(blockIdx.x) * 64, g0 = int64_t(blockIdx.y) * 64, k = blockIdx.z;
+  const int ng = int(groups - g0 < 64 ? groups - g0 : 64), t = int(threadIdx.x);
+  uint16_t v[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) {   // 64 ng elements, the loads in flight together
+    const int e = t + 256 * m, r = e / ng, g = e - r * ng;
+    v[m] = r < 64 && i0 + r < a.M ? src[(k * a.M + i0 + r) * groups + g0 + g] : uint16_t(0);
+  }
+#pragma unroll
+  for (int m = 0; m < 16; ++m) {
+    const int e = t + 256 * m, r = e / ng, g = e - r * ng;
+    if (r < 64) tile[g][r] = v[m];
+  }
+  __syncthreads();
+  uint32_t* dst = reinterpret_cast<uint32_t*>(a.base + a.off_rscale) + ((p0 + k * groups + g0) * a.Mp + i0) / 2;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {   // two rows per store
+    const int g = (t >> 5) + 8 * m, r = 2 * (t & 31);
+    if (g < ng) dst[int64_t(g) * (a.Mp / 2) + (t & 31)] = uint32_t(tile[g][r]) | (uint32_t(tile[g][r + 1]) << 16);
+  }
+}
+
+// Fine row scales, one thread per scale: a chunk's block of G planes holds, for each row, G consecutive scales; slot b is
+// the scale of the chunk's group (b + floor(i/n)) mod G (n = spc/G sub-vectors per group), i.e. the group read at
+// positions b*n .. b*n+n-1 of the row's rotated entry. src [K][M][groups], nc chunks per base, planes from p0.
+__global__ void k_pack_rscale_fine(PackArgs a, const uint16_t* src, int64_t groups, int64_t nc, int64_t G, int64_t p0,
+                                   int64_t count) {
+  const int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+  if (e >= count) return;
+  const int64_t blk = e / (a.Mp * G);                 // (base, chunk within the base)
+  const int64_t i = (e % (a.Mp * G)) / G;
+  const int64_t b = e % G;
+  const int64_t k = blk / nc, lc = blk % nc;
+  const int64_t n = (kChunk / a.mu) / G;
+  const int64_t grp = lc * G + (b + i / n) % G;
+  reinterpret_cast<uint16_t*>(a.base + a.off_rscale)[p0 * a.Mp + e] =
+      i < a.M && grp < groups ? src[(k * a.M + i) * groups + grp] : uint16_t(0);
 }
 
 // One thread per virtual column; the first NCP threads also write the chunk's row-scale plane, the first max(S,1)
-// threads the 16-bit salient indices.
-__global__ void k_pack_columns(PackArgs a) {
+// threads the 16-bit salient indices, the first 64 the header.
+__global__ void k_pack_columns(PackArgs a, HeaderWords h) {
   const int64_t v = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
+  if (v < 64) reinterpret_cast<uint32_t*>(a.base)[v] = h.w[v];
   if (v < a.V) {
     const int64_t c = v / kChunk;
     const int64_t r = v % kChunk;
@@ -213,11 +252,6 @@ __global__ void k_pack_columns(PackArgs a) {
   if (v < ns) {
     reinterpret_cast<uint16_t*>(a.base + a.off_sal_idx)[v] = (v < a.S) ? uint16_t(a.sal_idx[v]) : uint16_t(0);
   }
-}
-
-__global__ void k_write_header(HeaderWords h, uint32_t* dst) {
-  const int t = threadIdx.x;
-  if (t < 64) dst[t] = h.w[t];
 }
 
 // Reads one virtual sign bit (chunk c, column r of the chunk, row i) back from the device layout.
@@ -384,13 +418,22 @@ fluxbin_status launch_pack(const fluxbin_layer& L, const fluxbin_weights& w, con
   __builtin_memcpy(&hw, &h, sizeof(h));
 
   const int T = 256;
-  hipLaunchKernelGGL(k_write_header, dim3(1), dim3(64), 0, stream, hw, static_cast<uint32_t*>(L.d_base));
-  const int64_t n_sig = d.NSC * 2 * d.Mp;
-  hipLaunchKernelGGL(k_pack_signs, dim3(grid_for(n_sig, T)), dim3(T), 0, stream, a);
-  if (d.NRP * d.Mp > 0) hipLaunchKernelGGL(k_pack_rscale, dim3(grid_for(d.NRP * d.Mp, T)), dim3(T), 0, stream, a);
+  const bool sal = d.NRP > d.Pg;
+  hipLaunchKernelGGL(k_pack_signs, dim3(unsigned(d.Mp / kPackRows), grid_for(d.NCP, kPackChunks)), dim3(T), 0, stream, a);
+  auto rscale = [&](const uint16_t* src, int64_t K, int64_t groups, int64_t nc, int64_t G, int64_t p0) {
+    if (G == 1) {
+      hipLaunchKernelGGL(k_pack_rscale_planes, dim3(unsigned(d.Mp / 64), grid_for(groups, 64), unsigned(K)), dim3(T), 0,
+                         stream, a, src, groups, p0);
+    } else {
+      const int64_t n = K * nc * G * d.Mp;
+      hipLaunchKernelGGL(k_pack_rscale_fine, dim3(grid_for(n, T)), dim3(T), 0, stream, a, src, groups, nc, G, p0, n);
+    }
+  };
+  rscale(a.alpha_r, L.shape.Kb, d.Gr, d.ncg, d.Gcg, 0);
+  if (sal) rscale(a.alpha_sr, L.shape.Ks, d.Gs, d.ncs, d.Gcs, d.Pg);
   int64_t n_col = d.V;
   if (L.shape.S > n_col) n_col = L.shape.S;
-  hipLaunchKernelGGL(k_pack_columns, dim3(grid_for(n_col, T)), dim3(T), 0, stream, a);
+  hipLaunchKernelGGL(k_pack_columns, dim3(grid_for(n_col, T)), dim3(T), 0, stream, a, hw);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "launching the packing kernels");
   return FLUXBIN_OK;
