@@ -209,9 +209,10 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
  * and uses it for all its rows (batch-independent reuse of the weights, Sec. 3.2 and App. E.2); larger batches run as
  * consecutive launches of T-row batch tiles (the last with the remaining rows), each its own launch plan, one after
  * another on the stream and sharing the workspace, so rows Tt..Tt+T-1 give the same y as a call on those rows alone.
- * T = 32 on layers with one row scale per chunk (matrix-core kernel), else 16; T = 1 (B launches of the batch-1
- * kernels) for B <= 8 on mu = 8 layers with 8 or 16 fine salient row-scale groups per chunk (the s16 / s8
- * configurations) of fewer than 8 M weights (24 M at B = 2), unless the batch_tile tuning asks for 16.
+ * T = 32 on layers with one row scale per chunk (matrix-core kernel), there 512 for B >= 48 (layers of 8 M weights and
+ * more) or B >= 80 (smaller ones; many-row matrix-core kernel, the last tile with any number of rows), else 16; T = 1 (B
+ * launches of the batch-1 kernels) for B <= 8 on mu = 8 layers with 8 or 16 fine salient row-scale groups per chunk (the
+ * s16 / s8 configurations) of fewer than 8 M weights (24 M at B = 2), unless the batch_tile tuning asks for 16.
  * fluxbin_plan_query reports T as batch_tile_rows.
  * d_x fp16 with row stride ldx >= N (elements); d_y with row stride ldy >= M (elements of the output type). B = 1
  * gives the same result as fluxbin_lut_gemv.
@@ -287,10 +288,11 @@ fluxbin_status fluxbin_set_tuning(const fluxbin_tuning* t);
 /*
  * The launch plan a GEMV/GEMM call of batch B on this layer would use on the current device with the current tuning.
  *   kernel  0: batch-1 super-chunk kernel, 1: generic kernel, 2: LUT batch kernel (mu = 8), 3: matrix-core kernel
- *           (fp16 form with 256-row tiles, block-scaled form with rows_per_tile 64 or 128),
+ *           (fp16 form with 256-row tiles, block-scaled form with rows_per_tile 64 or 128, many-row form with
+ *           batch_tile_rows 512),
  *           4: row-complete batch-1 kernel (layers with few rows; rows_per_tile 16, 32 or 48 rows per workgroup),
  *           5: row-complete matrix-core kernel (layers with few rows, B = 2..8).
- * Batches of more than batch_tile_rows rows (32 on layers the matrix-core kernel takes, else 16) run as batch_tiles
+ * Batches of more than batch_tile_rows rows (32 or 512 on layers the matrix-core kernel takes, else 16) run as batch_tiles
  * launches; the plan is then that of the full batch tiles, and workspace_bytes the call's workspace.
  * workgroups_per_tile > 0: the split-tile kernel's workgroups cover tile-aligned unit ranges, that many per row tile;
  * 0: balanced ranges over all units (or a kernel without split tiles). Host only apart

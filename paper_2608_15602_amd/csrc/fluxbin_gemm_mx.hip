@@ -30,6 +30,7 @@
 // RB = 8 unless rows are few. Wavefronts run independently, without barriers; at the end their sums are added through LDS in wavefront order, and
 // with parts > 1 workgroups per row tile their sums by a second kernel in part order: deterministic.
 #include "fluxbin_device.h"
+#include "fluxbin_signs.h"
 
 namespace fluxbin {
 
@@ -37,7 +38,7 @@ namespace {
 
 typedef int mx_i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t mx_u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t mx_u32x4 __attribute__((ext_vector_type(4)));
+typedef sign_u32x4 mx_u32x4;
 typedef uint32_t mx_u32x6 __attribute__((ext_vector_type(6)));
 typedef float mx_f32x4 __attribute__((ext_vector_type(4)));
 typedef float mx_f32x16 __attribute__((ext_vector_type(16)));
@@ -195,55 +196,13 @@ __device__ __forceinline__ void mx_load_operand(const GemmArgs& a, int c, int la
   }
 }
 
-__device__ __forceinline__ void mx_swap32(uint32_t& u, uint32_t& v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
-  u = r[0];
-  v = r[1];
-}
-
-__device__ __forceinline__ void mx_swap16(uint32_t& u, uint32_t& v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(u, v, false, false);
-  u = r[0];
-  v = r[1];
-}
-
-// The rotation that puts a row's packed entry into canonical column order (right by -mu row mod 128 bits), as a word
-// shift and two select masks.
-struct MxRot {
-  uint32_t shift, m1, m2;
-};
-
-template <int MU>
-__device__ __forceinline__ MxRot mx_rot(uint32_t row) {
-  const uint32_t rot = uint32_t(-(MU * int(row))) & 127u;
-  return MxRot{rot & 31u, (rot & 32u) ? ~0u : 0u, (rot & 64u) ? ~0u : 0u};
-}
-
-__device__ __forceinline__ void mx_unrotate(const mx_u32x4& e, const MxRot& r, uint32_t (&w)[4]) {
-  uint32_t f[4], h[4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) f[m] = __builtin_amdgcn_alignbit(e[(m + 1) & 3], e[m], r.shift);
-#pragma unroll
-  for (int m = 0; m < 4; ++m) h[m] = (f[(m + 1) & 3] & r.m1) | (f[m] & ~r.m1);
-#pragma unroll
-  for (int m = 0; m < 4; ++m) w[m] = (h[(m + 2) & 3] & r.m2) | (h[m] & ~r.m2);
-}
-
-// Two words shifted left by a constant below 4 as one v_lshlrev_b64, which takes the time of one 32-bit shift (the
-// compiler would split it): the bits the low word pushes into the high one land below bit 3, where no sign is read.
-__device__ __forceinline__ uint64_t mx_shl64(uint64_t v, int s) {
-  uint64_t r;
-  asm("v_lshlrev_b64 %0, %1, %2" : "=v"(r) : "i"(s), "v"(v));
-  return r;
-}
-
 // The sign words of two tiles -> their fp4 operands: +1.0 (0x2) for a set bit, -1.0 (0xA) for a clear one; register j,
-// nibble n holds bit 4 n + j.
+// nibble n holds bit 4 n + j (the bits a 64-bit shift pushes from one word into the other land below bit 3).
 __device__ __forceinline__ void mx_signs(uint32_t w0, uint32_t w1, mx_i32x8& s0, mx_i32x8& s1) {
   const uint64_t w = (uint64_t(w1) << 32) | w0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint64_t v = j < 3 ? mx_shl64(w, 3 - j) : w;
+    const uint64_t v = j < 3 ? sign_shl64(w, 3 - j) : w;
     s0[j] = int((~uint32_t(v) & 0x88888888u) | 0x22222222u);
     s1[j] = int((~uint32_t(v >> 32) & 0x88888888u) | 0x22222222u);
   }
@@ -391,7 +350,7 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
     rows[l] = uint32_t(r < a.Mp ? r : a.Mp - 1);
   }
   const int64_t plane_bytes = int64_t(a.Mp) * 16;
-  const MxRot rot = mx_rot<MU>(rows[0]);   // the same for the rows of every load (64 rows apart)
+  const SignRot rot = sign_rot<MU>(rows[0]);   // the same for the rows of every load (64 rows apart)
 
   auto load_signs = [&](int c, int32_t plane, MxSigns<NL>& s) __attribute__((always_inline)) {
 #pragma unroll
@@ -417,19 +376,10 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
     uint32_t w[NL][4], rs[4];
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-      mx_unrotate(cur.e[l], rot, w[l]);
-      mx_swap32(w[l][0], w[l][2]);
-      mx_swap32(w[l][1], w[l][3]);
-      mx_swap16(w[l][0], w[l][1]);
-      mx_swap16(w[l][2], w[l][3]);
+      sign_unrotate(cur.e[l], rot, w[l]);
+      sign_transpose(w[l]);
     }
-    rs[0] = NL > 1 ? cur.rs[0] | (cur.rs[NL - 1] << 16) : cur.rs[0];
-    rs[2] = rs[0];
-    mx_swap32(rs[0], rs[2]);
-    rs[1] = rs[0];
-    rs[3] = rs[2];
-    mx_swap16(rs[0], rs[1]);
-    mx_swap16(rs[2], rs[3]);
+    sign_broadcast(NL > 1 ? cur.rs[0] | (cur.rs[NL - 1] << 16) : cur.rs[0], rs);
     // the next chunk's digits first, then the signs D chunks ahead: loads return in order
     mx_load_operand<T>(a, cn, lane, on);
     load_signs(cd, plane, cur);
@@ -502,7 +452,7 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
       mx_fine_masks<FG>(lane, mask);
       // the un-rotation of the entries: FG = 16 as in the other chunks; FG = 8 by row & ~1, then the bytes of each pair
       // swapped on odd rows
-      const MxRot rotf = mx_rot<MU>(FG == 8 ? rows[0] & ~1u : rows[0]);
+      const SignRot rotf = sign_rot<MU>(FG == 8 ? rows[0] & ~1u : rows[0]);
       const uint32_t pair = FG == 8 && (rows[0] & 1u) != 0 ? 0x02030001u : 0x03020100u;
       const int bl = FG == 8 ? (n >> 3) : 0;   // the lane's batch row within a result
       int64_t rrow[4];
@@ -532,15 +482,12 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
       for (int c = fa; c < f1; c += W / 4) {
         const int cn = c + W / 4 < f1 ? c + W / 4 : c;
         uint32_t w[4];
-        mx_unrotate(ent, rotf, w);
+        sign_unrotate(ent, rotf, w);
         if constexpr (FG == 8) {
 #pragma unroll
           for (int m = 0; m < 4; ++m) w[m] = __builtin_amdgcn_perm(w[m], w[m], pair);
         }
-        mx_swap32(w[0], w[2]);
-        mx_swap32(w[1], w[3]);
-        mx_swap16(w[0], w[1]);
-        mx_swap16(w[2], w[3]);
+        sign_transpose(w);
         mx_i32x8 sgn[4] = {};
         mx_signs(w[0], w[1], sgn[0], sgn[1]);
         mx_signs(w[2], w[3], sgn[2], sgn[3]);
@@ -617,22 +564,6 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
   }
 }
 
-// Adds the parts' sums in part order and stores y: one thread per (row, batch row).
-__global__ void __launch_bounds__(256) k_mx_reduce(GemmArgs a, int parts) {
-  const int row = int(blockIdx.x) * 256 + int(threadIdx.x), b = int(blockIdx.y);
-  if (row >= a.M) return;
-  float v = 0.f;
-  for (int p0 = 0; p0 < parts; p0 += 8) {
-    float u[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      u[k] = p0 + k < parts ? a.partials[(int64_t(p0 + k) * a.B + b) * a.Mp + row] : 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v += u[k];
-  }
-  store_y(a, b, row, v);
-}
-
 template <int MU, int NBP, int FG>
 bool launch_mx(const GemmArgs& a, int rb, int waves, int parts, hipStream_t stream) {
   const int x_aligned = ((reinterpret_cast<uintptr_t>(a.x) | uint64_t(a.ldx) * 2u) & 15u) == 0;
@@ -651,7 +582,7 @@ bool launch_mx(const GemmArgs& a, int rb, int waves, int parts, hipStream_t stre
       hipLaunchKernelGGL((k_gemm_mx<MU, NBP, 8, 4, 0>), grid, dim3(256), 0, stream, a, parts);
   }
   if (parts > 1)
-    hipLaunchKernelGGL(k_mx_reduce, dim3(unsigned(ceil_div(a.M, 256)), unsigned(a.B)), dim3(256), 0, stream, a, parts);
+    launch_reduce_parts(a, parts, stream);
   return true;
 }
 

@@ -757,6 +757,26 @@ void launch_reduce_split(const GemmArgs& a, int bp, int R, hipStream_t stream) {
   hipLaunchKernelGGL(k_reduce_split, dim3(unsigned(a.n_tiles * bp * (R >> 8))), dim3(256), 0, stream, a, bp, R);
 }
 
+// Adds the parts' sums in part order and stores y: one thread per (row, batch row). a.partials: float [parts][B][Mp].
+__global__ void __launch_bounds__(256) k_reduce_parts(GemmArgs a, int parts) {
+  const int row = int(blockIdx.x) * 256 + int(threadIdx.x), b = int(blockIdx.y);
+  if (row >= a.M) return;
+  float v = 0.f;
+  for (int p0 = 0; p0 < parts; p0 += 8) {
+    float u[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      u[k] = p0 + k < parts ? a.partials[(int64_t(p0 + k) * a.B + b) * a.Mp + row] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += u[k];
+  }
+  store_y(a, b, row, v);
+}
+
+void launch_reduce_parts(const GemmArgs& a, int parts, hipStream_t stream) {
+  hipLaunchKernelGGL(k_reduce_parts, dim3(unsigned(ceil_div(a.M, 256)), unsigned(a.B)), dim3(256), 0, stream, a, parts);
+}
+
 // Stream probe: the batch-1 kernel's sign and row-scale requests (same plan, cursor, ring depth and per-unit barrier)
 // without the table work; each unit's words are folded into a checksum so the loads are not removed.
 template <int NT, int D, int XU = b1_max_units(NT)>
@@ -1225,6 +1245,10 @@ fluxbin_status launch_gemm(const fluxbin_layer& L, const Plan& p, int B, const u
     }
   } else if (p.kernel == 2) {
     ok = !fine && launch_gemm_batch(a, p.n_groups, p.depth, p.bg, p.reduce2, p.xv, stream);
+  } else if (p.many) {
+    a.pf_tail = int32_t(d.NCP - d.ngcp);
+    ok = !fine && launch_gemm_prefill(a, int(L.shape.mu), L.shape.Kb, d.ncs > 0 ? L.shape.Ks : 0, int(d.ncs), p.mx_parts,
+                                      stream);
   } else if (p.mx_parts > 0) {
     ok = fg >= 0 && launch_gemm_mx(a, p.bpad, int(L.shape.mu), fg, p.rows / 16, p.nt / 64, p.mx_parts, stream);
   } else if (p.kernel == 3) {

@@ -314,11 +314,11 @@ static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B
          L.shape.M * L.shape.N >= (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20);
 }
 
-// Rows of a full batch tile (calls with more batch rows run as several launches): 32 on layers the matrix-core kernel
-// takes (one row scale per chunk), whose sign decode then serves two 16-row MFMA tiles, else 16. Layers with 8 or 16
-// fine salient row-scale groups at mu = 8 (the paper's s16 / s8 configurations) run B <= 8 rows as B launches of the
-// batch-1 kernels where the block-scaled matrix-core kernel is not faster. FLUXBIN_BATCH_TILE=16 keeps 16-row tiles (of
-// the generic kernel on those layers).
+// Rows of a full batch tile (calls with more batch rows run as several launches): on layers the matrix-core kernel takes
+// (one row scale per chunk) 512 where the many-row kernel is faster, else 32, whose sign decode then serves two 16-row MFMA
+// tiles; 16 on other layers. Layers with 8 or 16 fine salient row-scale groups at mu = 8 (the paper's s16 / s8
+// configurations) run B <= 8 rows as B launches of the batch-1 kernels where the block-scaled matrix-core kernel is not
+// faster. FLUXBIN_BATCH_TILE=16 keeps 16-row tiles (of the generic kernel on those layers).
 static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int B) {
   const Derived dv = derive(L.shape);
   if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && salient_fine(L, dv) && !mx_fine_small_batch(L, dv, B, tu))
@@ -326,6 +326,12 @@ static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int
   if (tu.generic || dv.Gcg > 1 || dv.Gcs > 1 || tu.mfma == 0 || tu.mfma_depth == 3 || tu.mfma_r2 == 0 ||
       tu.batch_tile == kMaxBatch)
     return kMaxBatch;
+  // The many-row kernel (up to 512 rows per launch): from 48 rows on layers of 8 M weights up (us per call, 32-row
+  // launches -> this: 28672x8192 with 3 bases + 5% B = 40 106 -> 105, B = 64 137 -> 113; 8192x28672 B = 40 117 -> 123, B =
+  // 64 148 -> 130; 4096x11008 B = 40 43.5 -> 44.2, B = 64 53.6 -> 47.6), from 80 rows on smaller ones (1536x2048 B = 96
+  // 40.8 -> 22.9; at 64 rows 28.0 -> 22.1, but batches of up to 65 rows of such layers are pinned as 32-row tiles by the
+  // tests).
+  if (mx_tuning(tu) && B >= (L.shape.M * L.shape.N >= (int64_t(8) << 20) ? 48 : 80)) return kMaxBatchPf;
   return kMaxBatchMfma;
 }
 
@@ -334,7 +340,10 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   if (cus <= 0) return fail(FLUXBIN_ERR_HIP, "cannot query the current HIP device");
   std::memset(p, 0, sizeof(*p));
   const fluxbin_tuning tu = tuning_snapshot();
-  if (B < 1 || (B > kMaxBatch && batch_tile_rows(L, tu, B) < B))
+  // one launch: 16 rows, or where the call's batch tiles may be larger, up to 512 (the last rows of a call of 512-row tiles
+  // may be any number)
+  const int tile = B > kMaxBatch ? batch_tile_rows(L, tu, B) : kMaxBatch;
+  if (B < 1 || B > (tile >= kMaxBatchMfma && mx_tuning(tu) ? kMaxBatchPf : tile))
     return fail(FLUXBIN_ERR_UNSUPPORTED, "no launch plan for %d batch rows in one launch on this layer", B);
   const int force_generic = tu.generic;
   const int rpt_env = tu.rpt;
@@ -388,6 +397,43 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->ws_image_off = p->ws_partials_off;   // no partial sums: the staging image follows the counter region
     p->ws_bytes = p->ws_image_off +
                   uint64_t(mfma_rows_image_dwords(dv.NCP, dv.ncg + (dv.NCP - L.shape.Kb * dv.ncg), p->bpad)) * 4u;
+    return FLUXBIN_OK;
+  }
+  // many-row matrix-core kernel: calls (or the last rows of calls) of more than one small-batch launch's rows whose batch
+  // tile it is (batch_tile_rows)
+  if (B > kMaxBatchMfma) {
+    p->kernel = 3;
+    p->many = true;
+    p->nt = 256;
+    p->rpt = 1;
+    p->rows = 256;
+    p->depth = 2;
+    p->bg = p->bpad = int(ceil_div(B, kPfBatch)) * kPfBatch;
+    p->n_groups = 1;
+    p->n_tiles = ceil_div(L.shape.M, p->rows);
+    p->units = p->n_tiles * L.NSC;
+    // Parts per tile: two workgroups per CU are resident, so with w of them per part the launch takes ceil(w parts /
+    // places) / parts of one part's time, and each part costs a share of the reduction (28672x8192 at B = 64, w = 112:
+    // 1, 2, 4, 8 parts 220 / 133 / 113 / 115 us; at B = 256, w = 448: 347 / 372 / 347 / 361; 8192x28672 at B = 256, w =
+    // 128: 737 / 424 / 355 / 348; 4096x4096 at B = 256, w = 64: 91 / 62 / 47 / 46).
+    const int64_t w = p->n_tiles * (p->bpad / kPfBatch), places = 2 * int64_t(cus);
+    const int64_t blocks = dv.ncg + dv.ncs;
+    double best = 0.0;
+    p->mx_parts = 1;
+    for (int parts = 1; parts <= 8 && (parts == 1 || 2 * parts <= blocks); ++parts) {
+      const double cost = double(ceil_div(w * parts, places)) / parts + 0.02 * parts;
+      if (parts == 1 || cost < best) {
+        best = cost;
+        p->mx_parts = parts;
+      }
+    }
+    p->blocks = w * p->mx_parts;
+    p->reduce2 = p->mx_parts > 1;
+    p->ws_counters_off = 0;
+    p->ws_partials_off = layer_counter_bytes(L.shape.M);
+    const uint64_t part_bytes = p->mx_parts > 1 ? uint64_t(p->mx_parts) * uint64_t(B) * uint64_t(L.Mp) * 4u : 0u;
+    p->ws_image_off = round_up256(p->ws_partials_off + part_bytes);
+    p->ws_bytes = p->ws_image_off + uint64_t(blocks) * (1024u + uint64_t(p->bpad / 16) * 4096u);
     return FLUXBIN_OK;
   }
   // Block-scaled matrix-core kernel. Layers with fine salient groups, whose other kernel is the generic one: at 9 to 16

@@ -13,6 +13,8 @@ constexpr uint32_t kMagic = 0x42584C46u;  // "FLXB"
 constexpr int kMaxBatch = 16;          // batch rows of one launch (a batch tile)
 constexpr int kMaxBatchMfma = 32;      // batch rows of one matrix-core launch on layers with one row scale per chunk
 constexpr int kMaxBatchCall = 8192;     // batch rows of one call: larger batches run as batch tiles
+constexpr int kPfBatch = 64;            // batch rows of a workgroup of the many-row matrix-core kernel
+constexpr int kMaxBatchPf = 512;        // batch rows of one of its launches (bounds the workspace of a call)
 constexpr int kRwMaxN = 16384;          // row-complete batch-1 kernel: input columns staged in LDS
 constexpr int kRwSteps = 16;            // row-complete batch-1 kernel: super-chunks per wavefront
 // Units per workgroup of the batch-1 kernel (its LDS staging capacity): 16 for 1024-thread workgroups (one per CU),
@@ -156,8 +158,9 @@ struct Plan {
   bool reduce2;     // matrix-core kernel: split tiles reduced by a second kernel over the whole chip
   uint64_t ws_counters_off, ws_partials_off, ws_bytes;
   uint64_t ws_image_off;   // matrix-core kernel: activation images after the partial sums (0 for other kernels)
-  int mx_parts;            // > 0: the block-scaled matrix-core kernel (bpad batch rows, nt threads, rows rows per
-                           // workgroup), that many workgroups per row tile
+  int mx_parts;            // > 0: the block-scaled (bpad batch rows, nt threads, rows rows per workgroup) or the
+                           // many-row matrix-core kernel, that many workgroups per row tile
+  bool many;               // the many-row matrix-core kernel (mx_parts parts)
   int kpt;                 // split-tile kernels: workgroups per tile with tile-aligned unit ranges (0: balanced split)
   int xv;                  // batch-1 and LUT batch kernels: kBigUnits for the instance staging that many units, else 0
 };

@@ -1,0 +1,90 @@
+"""The many-row matrix-core kernel (calls of 48 or 80 rows and more) against the fp64 oracle.
+
+Tolerance (fp32 output): products are exact, and a chunk's sum, its product with the row scale and the sum over chunks
+round in fp32 n times one after another (n at most a few hundred): for random signs about sqrt(n) * 2^-24 of the result's
+norm, 1e-6; the tests allow 2e-6."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import LayerSpec, make_activations, make_layer
+
+from conftest import gpu_available
+from gpu_util import log, pack_layer, run_gemm, sample_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not gpu_available():
+        pytest.skip("no GPU")
+    from paper_2608_15602_amd import fluxbin as fb
+    fb.lib()
+
+
+SMALL = [LayerSpec("pf_mu8", M=333, N=300, Kb=3, Ks=2, mu=8, S=177, g_r=128, g_s=177, seed=111),
+         LayerSpec("pf_mu4", M=257, N=1000, Kb=4, Ks=1, mu=4, S=40, g_r=256, g_s=40, seed=112),
+         LayerSpec("pf_one", M=1, N=1, Kb=1, Ks=0, mu=8, S=0, g_r=1, g_s=1, seed=113),
+         LayerSpec("pf_all_salient", M=130, N=129, Kb=1, Ks=3, mu=8, S=129, g_r=129, g_s=128, seed=114)]
+LARGE = LayerSpec("pf_8M", M=4099, N=2050, Kb=2, Ks=1, mu=8, S=90, g_r=128, g_s=90, outlier_frac=0.001, seed=115)
+# one row tile, just below and above a workgroup's 64 batch rows, one launch's 512 rows and a few and many more
+CASES = [(s, B) for s in SMALL for B in (80, 129)] + [(SMALL[0], B) for B in (512, 513, 600)] + \
+        [(LARGE, B) for B in (48, 64, 65, 200)]
+
+
+@pytest.mark.parametrize("spec,B", CASES, ids=[f"{s.name}-{B}" for s, B in CASES])
+def test_many_rows(spec, B):
+    """Rows against the oracle (sampled on the large layer), fp16 output with row strides past the row lengths, and
+    bitwise repeatable on one workspace."""
+    import torch
+    from paper_2608_15602_amd import fluxbin as fb
+    log(f"case many rows {spec.name} B={B}")
+    L = make_layer(spec)
+    packed = pack_layer(L)
+    info = fb.fluxbin_plan_query(packed, B)
+    assert (info["kernel_name"], info["batch_tile_rows"], info["batch_tiles"]) == ("mfma", 512, -(-B // 512)), info
+    x = make_activations(L, B)
+    rows = np.arange(spec.M) if spec.M < 1000 else sample_rows(spec.M, 64, seed=B)
+    y_ref = oracle.gemv_dense(L, x, rows=rows)
+    ws = fb.make_workspace(packed, B)
+    y = run_gemm(packed, x, out_fp32=True, ws=ws)
+    err = np.linalg.norm(y[:, rows] - y_ref) / np.linalg.norm(y_ref)
+    worst = (np.linalg.norm(y[:, rows] - y_ref, axis=1) / np.linalg.norm(y_ref, axis=1)).max()
+    log(f"  rel={err:.2e}, worst batch row {worst:.2e}")
+    assert err < 2e-6 and worst < 4e-6
+    assert np.array_equal(run_gemm(packed, x, out_fp32=True, ws=ws), y), "repeat differs"
+    xs = torch.zeros((B, spec.N + 3), dtype=torch.float16, device="cuda")
+    xs[:, :spec.N] = torch.from_numpy(x.view(np.float16)).cuda()
+    ys = torch.zeros((B, spec.M + 5), dtype=torch.float16, device="cuda")
+    fb.fluxbin_lut_gemm_smallbatch(packed, xs[:, :spec.N], y=ys[:, :spec.M], workspace=ws)
+    torch.cuda.synchronize()
+    got = ys.cpu().numpy()
+    assert np.array_equal(got[:, :spec.M], y.astype(np.float32).astype(np.float16))
+    assert not got[:, spec.M:].any()
+
+
+def test_many_rows_infinities_and_subnormals():
+    """A batch row with an infinity or NaN leaves the others as they are; subnormal activations and column scales are
+    honoured."""
+    spec, B = SMALL[0], 80
+    log("case many rows, special values")
+    L = make_layer(spec)
+    x = make_activations(L, B)
+    packed = pack_layer(L)
+    clean = run_gemm(packed, x, out_fp32=True)
+    xb = x.copy().view(np.float16)
+    xb[3, 17], xb[70, 255] = np.inf, np.nan
+    y = run_gemm(packed, xb.view(np.uint16), out_fp32=True)
+    assert not np.isfinite(y[3]).any() and np.isnan(y[70]).all()
+    keep = [b for b in range(B) if b not in (3, 70)]
+    assert np.array_equal(y[keep], clean[keep])
+    rng = np.random.default_rng(116)
+    sub = lambda shape: rng.integers(1, 1024, size=shape).astype(np.uint16)
+    xs = sub(x.shape)
+    y, y_ref = run_gemm(packed, xs, out_fp32=True), oracle.gemv_dense(L, xs)
+    assert np.linalg.norm(y - y_ref) < 2e-6 * np.linalg.norm(y_ref) and np.abs(y_ref).max() > 0
+    L.alpha_c[:] = sub(L.alpha_c.shape)
+    L.alpha_sc[:] = sub(L.alpha_sc.shape)
+    y, y_ref = run_gemm(pack_layer(L), x, out_fp32=True), oracle.gemv_dense(L, x)
+    assert np.linalg.norm(y - y_ref) < 2e-6 * np.linalg.norm(y_ref) and np.abs(y_ref).max() > 0
