@@ -265,10 +265,10 @@ bool launch_gemm_mfma(const GemmArgs& a, int bpad, int mu, int depth, bool reduc
 // 64 waves threads, bpad = 4 or 8 padded batch rows; false if no instance exists or the layer exceeds its limits.
 bool launch_gemm_mfma_rows(const GemmArgs& a, int bpad, int mu, int waves, int rb, hipStream_t stream);
 
-// Block-scaled matrix-core kernel (fluxbin_gemm_mx.hip): 16 rb rows per workgroup of `waves` wavefronts, nbp = 2, 4, 8
-// or 16 padded batch rows, `parts` workgroups per row tile (their sums added by a second kernel); false if no instance
-// exists. fg: 0, or 8 / 16 for layers with that many fine groups per salient chunk (mu = 8, rb = 4, waves = 8).
-bool launch_gemm_mx(const GemmArgs& a, int nbp, int mu, int fg, int rb, int waves, int parts, hipStream_t stream);
+// Block-scaled matrix-core kernel (fluxbin_gemm_mx.hip): nbp = 2, 4, 8 or 16 padded batch rows, `parts` workgroups per
+// row tile (their sums added by a second kernel); false if no instance exists. fg: 0, or 8 / 16 for layers with that many
+// fine groups per salient chunk (mu = 8).
+bool launch_gemm_mx(const GemmArgs& a, int nbp, int mu, int fg, int parts, hipStream_t stream);
 
 // Adds the sums of `parts` workgroups per row tile, a.partials [parts][B][Mp], in part order into y (fluxbin_gemv.hip).
 void launch_reduce_parts(const GemmArgs& a, int parts, hipStream_t stream);

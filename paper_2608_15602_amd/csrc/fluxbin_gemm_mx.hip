@@ -15,8 +15,10 @@
 //
 // Precision. p is exact in fp32 (two 11-bit significands). Digit d of a 32-column block is p's remainder rounded to
 // fp6 at scale 2^(E - 1 - 5 d), E the exponent of the block's largest |p|: magnitudes up to 4, rounded to 2^-3 of the
-// scale at most. After the kDigits = 6 digits the remainder is at most 2^-29 of the block's largest |p| (an fp32 sum
-// rounds at 2^-24 of its running value). Digit products +-q are
+// scale at most. After six digits the remainder is at most 2^-29 of the block's largest |p|, after the five of 9 to 16
+// batch rows (five instructions instead of six) 2^-24 (an fp32 sum rounds at 2^-24 of its running value). Relative error
+// against fp64 at 16 rows, fp16 kernel / five digits: 10240x8192 1.28e-7 / 1.13e-7, 5120x13824 1.46e-7 / 1.29e-7, 700x1000
+// 1.08e-7 / 0.99e-7. Digit products +-q are
 // exact, and they are summed in the matrix core's fp32 accumulation; row scale and chunk order are as in the other
 // kernels. Blocks with an infinity or NaN (in x or in a column scale) get zero digits and a mark, and are added by
 // scalar fp32 code after the matrix instructions.
@@ -44,13 +46,13 @@ typedef float mx_f32x4 __attribute__((ext_vector_type(4)));
 typedef float mx_f32x16 __attribute__((ext_vector_type(16)));
 typedef float mx_f32x32 __attribute__((ext_vector_type(32)));
 
-constexpr int kDigits = kMxDigits;
+constexpr int kDigits = mx_digits(1, true);   // of the fine groups' results (any number of batch rows)
 constexpr uint32_t kMxOdd = 0x80000000u;   // in a lane's last scale word, whose top byte no instruction uses
 
 // Digits per instruction and instructions per chunk with nbp padded batch rows (2, 4, 8 or 16): operand row m of
 // instruction t holds digit t * (16 / nbp) + m / nbp of batch row m mod nbp.
-template <int NBP>
-constexpr int mx_t() { return mx_instr(NBP); }
+template <int NBP, bool FINE>
+constexpr int mx_t() { return mx_instr(NBP, FINE); }
 
 // ---------------------------------------------------------------------------------------------------------------------
 // Image: per chunk T digit operands (64 lanes x 16 bytes, then 64 lanes x 8 bytes each) and the lanes' block scales.
@@ -66,11 +68,11 @@ __device__ __forceinline__ mx_u32x6 mx_to_fp6(const mx_f32x16& lo, const mx_f32x
 }
 
 // One thread per (chunk, 32-column block g, padded batch row): all digits of its 32 products. Batch rows past B, columns
-// without a source and digits past kDigits are zero. Bound by latency: column scales and activations in one round trip
+// without a source and digits past the last are zero. Bound by latency: column scales and activations in one round trip
 // (salient chunks: the indices in another before it), then about 400 instructions.
-template <int NBP>
+template <int NBP, bool FINE>
 __global__ void __launch_bounds__(64) k_mx_image(GemmArgs a, int x_aligned) {
-  constexpr int T = mx_t<NBP>(), DP = 16 / NBP;
+  constexpr int ND = mx_digits(NBP, FINE), T = mx_t<NBP, FINE>(), DP = 16 / NBP;
   const int tid = int(blockIdx.x) * 64 + int(threadIdx.x);
   const int b = tid & (NBP - 1), g = (tid / NBP) & 3, c = tid / (4 * NBP);
   if (c >= a.NCP) return;
@@ -136,10 +138,10 @@ __global__ void __launch_bounds__(64) k_mx_image(GemmArgs a, int x_aligned) {
   for (int d = 0; d < T * DP; ++d) {
     const int t = d / DP, lane = b + NBP * (d % DP) + 16 * g;
     mx_u32x6 q = {0, 0, 0, 0, 0, 0};
-    if (d < kDigits) {
+    if (d < ND) {
       const float sc = __builtin_bit_cast(float, (e0 - 5u * uint32_t(d)) << 23);
       q = mx_to_fp6(lo, hi, sc);
-      if (d + 1 < kDigits) {
+      if (d + 1 < ND) {
         const mx_f32x32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(q, sc);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -158,7 +160,7 @@ __global__ void __launch_bounds__(64) k_mx_image(GemmArgs a, int x_aligned) {
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       const int d = t * DP + dd;
-      w[t >> 2] |= (e0 - 5u * uint32_t(d < kDigits ? d : 0)) << (8 * (t & 3));
+      w[t >> 2] |= (e0 - 5u * uint32_t(d < ND ? d : 0)) << (8 * (t & 3));
     }
     if (odd && dd == 0) w[T > 4 ? 1 : 0] |= kMxOdd;
     uint32_t* dst = reinterpret_cast<uint32_t*>(img + T * 1536) + (b + NBP * dd + 16 * g) * (T > 4 ? 2 : 1);
@@ -296,7 +298,7 @@ struct MxFineOperand {
 
 template <int NBP>
 __device__ __forceinline__ void mx_load_fine(const GemmArgs& a, int c, int b, int lane, MxFineOperand<NBP>& o) {
-  constexpr int T = mx_t<NBP>(), DP = 16 / NBP;
+  constexpr int T = mx_t<NBP, true>(), DP = 16 / NBP;
   const uint8_t* img = reinterpret_cast<const uint8_t*>(a.img) + int64_t(c) * mx_chunk_bytes(T);
 #pragma unroll
   for (int d = 0; d < kDigits; ++d) {
@@ -327,7 +329,7 @@ struct MxSigns {
 // are spread over enough wavefronts.
 template <int MU, int NBP, int RB, int W, int FG>
 __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
-  constexpr int T = mx_t<NBP>();
+  constexpr int T = mx_t<NBP, (FG > 0)>();
   static_assert(RB == 4 || RB == 8, "whole loads of four row blocks");
   constexpr int NL = RB / 4;         // loads per chunk
   constexpr int D = 4 / NL;          // chunks requested ahead: 4 KB (and the row scales) per wavefront
@@ -565,47 +567,38 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
 }
 
 template <int MU, int NBP, int FG>
-bool launch_mx(const GemmArgs& a, int rb, int waves, int parts, hipStream_t stream) {
+bool launch_mx(const GemmArgs& a, int parts, hipStream_t stream) {
   const int x_aligned = ((reinterpret_cast<uintptr_t>(a.x) | uint64_t(a.ldx) * 2u) & 15u) == 0;
   if (parts < 1 || a.B < 1 || a.B > NBP) return false;
-  hipLaunchKernelGGL((k_mx_image<NBP>), dim3(unsigned(ceil_div(int64_t(a.NCP) * 4 * NBP, 64))), dim3(64), 0, stream, a,
-                     x_aligned);
-  const dim3 grid(unsigned(ceil_div(a.M, 16 * rb)), unsigned(parts));
-  if constexpr (FG != 0) {
-    if (rb != 4 || waves != 8) return false;
-    hipLaunchKernelGGL((k_gemm_mx<MU, NBP, 4, 8, FG>), grid, dim3(512), 0, stream, a, parts);
-  } else {
-    if (rb != 8 || (waves != 4 && waves != 8)) return false;
-    if (waves == 8)
-      hipLaunchKernelGGL((k_gemm_mx<MU, NBP, 8, 8, 0>), grid, dim3(512), 0, stream, a, parts);
-    else
-      hipLaunchKernelGGL((k_gemm_mx<MU, NBP, 8, 4, 0>), grid, dim3(256), 0, stream, a, parts);
-  }
+  hipLaunchKernelGGL((k_mx_image<NBP, (FG > 0)>), dim3(unsigned(ceil_div(int64_t(a.NCP) * 4 * NBP, 64))), dim3(64), 0,
+                     stream, a, x_aligned);
+  constexpr int RB = mx_rows(FG > 0) / 16;
+  hipLaunchKernelGGL((k_gemm_mx<MU, NBP, RB, 8, FG>), dim3(unsigned(ceil_div(a.M, 16 * RB)), unsigned(parts)), dim3(512), 0,
+                     stream, a, parts);
   if (parts > 1)
     launch_reduce_parts(a, parts, stream);
   return true;
 }
 
 template <int MU, int FG>
-bool launch_mx_b(const GemmArgs& a, int nbp, int rb, int waves, int parts, hipStream_t stream) {
+bool launch_mx_b(const GemmArgs& a, int nbp, int parts, hipStream_t stream) {
   switch (nbp) {
-    case 2: return launch_mx<MU, 2, FG>(a, rb, waves, parts, stream);
-    case 4: return launch_mx<MU, 4, FG>(a, rb, waves, parts, stream);
-    case 8: return launch_mx<MU, 8, FG>(a, rb, waves, parts, stream);
-    case 16:   // layers with fine groups only (the launch plan)
-      if constexpr (FG != 0) return launch_mx<MU, 16, FG>(a, rb, waves, parts, stream);
+    case 2: return launch_mx<MU, 2, FG>(a, parts, stream);
+    case 4: return launch_mx<MU, 4, FG>(a, parts, stream);
+    case 8: return launch_mx<MU, 8, FG>(a, parts, stream);
+    case 16: return launch_mx<MU, 16, FG>(a, parts, stream);
   }
   return false;
 }
 
 }  // namespace
 
-bool launch_gemm_mx(const GemmArgs& a, int nbp, int mu, int fg, int rb, int waves, int parts, hipStream_t stream) {
-  if (mu == 4) return fg == 0 && launch_mx_b<4, 0>(a, nbp, rb, waves, parts, stream);
+bool launch_gemm_mx(const GemmArgs& a, int nbp, int mu, int fg, int parts, hipStream_t stream) {
+  if (mu == 4) return fg == 0 && launch_mx_b<4, 0>(a, nbp, parts, stream);
   switch (fg) {
-    case 0: return launch_mx_b<8, 0>(a, nbp, rb, waves, parts, stream);
-    case 8: return launch_mx_b<8, 8>(a, nbp, rb, waves, parts, stream);
-    case 16: return launch_mx_b<8, 16>(a, nbp, rb, waves, parts, stream);
+    case 0: return launch_mx_b<8, 0>(a, nbp, parts, stream);
+    case 8: return launch_mx_b<8, 8>(a, nbp, parts, stream);
+    case 16: return launch_mx_b<8, 16>(a, nbp, parts, stream);
   }
   return false;
 }

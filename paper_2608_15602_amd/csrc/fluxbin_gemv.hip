@@ -1250,7 +1250,7 @@ fluxbin_status launch_gemm(const fluxbin_layer& L, const Plan& p, int B, const u
     ok = !fine && launch_gemm_prefill(a, int(L.shape.mu), L.shape.Kb, d.ncs > 0 ? L.shape.Ks : 0, int(d.ncs), p.mx_parts,
                                       stream);
   } else if (p.mx_parts > 0) {
-    ok = fg >= 0 && launch_gemm_mx(a, p.bpad, int(L.shape.mu), fg, p.rows / 16, p.nt / 64, p.mx_parts, stream);
+    ok = fg >= 0 && launch_gemm_mx(a, p.bpad, int(L.shape.mu), fg, p.mx_parts, stream);
   } else if (p.kernel == 3) {
     ok = !fine && launch_gemm_mfma(a, p.bpad, int(L.shape.mu), p.depth, p.reduce2, stream);
   } else if (p.kernel == 5) {

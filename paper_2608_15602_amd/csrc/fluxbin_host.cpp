@@ -439,41 +439,38 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   // Block-scaled matrix-core kernel. Layers with fine salient groups, whose other kernel is the generic one: at 9 to 16
   // rows always (us per call, generic -> this, s16 / s8: 128x256 15.5 -> 12.5 / 15.8 -> 15.9, 1024x1024 33.5 -> 13.7 /
   // 33.5 -> 15.9, 4096x11008 203 -> 32.7 / 197 -> 35.8), at up to 8 rows (calls of that many rows, and the last rows of
-  // larger batches) from 2^19 weights (6 rows: 512x1024 13.6 -> about 12.5, 256x384 10.6 -> about 12.5). Layers with one row scale per chunk at B <= 8,
-  // where neither the LUT batch kernel nor the row-complete matrix-core kernel is chosen, from 270 tiles of 16 rows x
-  // 128 columns per CU: its image kernel and (with several workgroups per row tile) its reduction cost 5 to 9 us, its
-  // matrix part less than half of the fp16 kernel's. us per call, fp16 kernel -> this one, B = 8: 11008x4096 2+1 (180
-  // tiles per CU) 15.7 -> 16.2, 4096x11008 16.7 -> 17.7; 5120x13824 2 bases (270) 19.6 -> 17.9; 8192x8192 3+1 (392)
-  // 22.1 -> 21.2; 28672x8192 2+1 / 3+1 35.0 -> 28.8 / 48.1 -> 38.3; 57344x8192 2+1 63.0 -> 48.5; B = 2, mu = 4:
-  // 28672x8192 3+1 42.9 -> 29.2. At 9 to 16 rows (twice the instructions and digit bytes) it is no faster there: 49.8
-  // against 50.3.
+  // larger batches) from 2^19 weights (6 rows: 512x1024 13.6 -> about 12.5, 256x384 10.6 -> about 12.5). Layers with one
+  // row scale per chunk, where neither the LUT batch kernel nor the row-complete matrix-core kernel is chosen, from 200
+  // (at 9 to 16 rows 190) tiles of 16 rows x 128 columns per CU: its image kernel and (with several workgroups per row
+  // tile) its reduction cost 5 to 9 us, its matrix part less than half of the fp16 kernel's. us per call, fp16 kernel ->
+  // this one, B = 8: 11008x4096 2+1 bases (180 tiles per CU) 15.5 -> 16.8; two bases 8192x6144 and 16384x3072 (192) 14.9 ->
+  // 15.5 and 14.8 -> 15.5; 8192x6144 2+1 (204) 16.7 -> 16.6; 10240x5120 (200) 17.4 -> 16.0; 4096x13824 (216) 18.0 -> 16.2;
+  // 8192x8192 3+1 (392) 22.1 -> 21.2; 28672x8192 2+1 / 3+1 35.0 -> 28.8 / 48.1 -> 38.3; 57344x8192 2+1 63.0 -> 48.1. B =
+  // 2, mu = 4: 28672x8192 3+1 42.9 -> 29.2. B = 16: 11008x4096 2+1 18.8 -> 20.2; 8192x6144 (192) 18.7 -> 17.3;
+  // 4096x13824 21.8 -> 18.6; 28672x8192 3+1 51 -> 47; 57344x8192 2+1 67 -> 61. A launch whose
+  // last wave of workgroups is mostly empty is left to the fp16 kernel, which splits the work evenly, at 9 to 16 rows
+  // (40000x8192 2+1, 313 tiles on 256 CUs: 56 -> 58; 20000x8192, 157 tiles: 31.5 -> 33.2) and, with more tiles than
+  // CUs, at 5 to 8 (two bases 36000x4096 26.2 -> 28.2, 34000x3072 21.9 -> 24.0; 20000x8192 27.9 -> 26.5). At up to 4 rows
+  // it is faster all the same (mu = 4: 36000x4096 24.3 -> 20.9).
+  const int64_t mx_n = ceil_div(L.shape.M, mx_rows(false)), mx_p = cus / mx_n > 1 ? cus / mx_n : 1;
+  const bool mx_full = 4 * mx_n * mx_p >= 3 * ceil_div(mx_n * mx_p, cus) * cus;
   if (B >= 2 && B <= kMaxBatch && mx_tuning(tu) &&
       ((b1_fine_ok && (B > 8 || L.shape.M * L.shape.N >= (int64_t(1) << 19))) ||
-       (!fine && B <= 8 && use_mfma(L, B, cus, tu) &&
-        ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(270) * cus))) {
+       (!fine && use_mfma(L, B, cus, tu) && (mx_full || B <= 4 || (B <= 8 && mx_n <= cus)) &&
+        ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(B <= 8 ? 200 : 190) * cus))) {
     p->kernel = 3;
     p->bg = B <= 2 ? 2 : (B <= 4 ? 4 : (B <= 8 ? 8 : 16));
     p->bpad = p->bg;
     p->n_groups = 1;
     p->rpt = 1;
     p->depth = 2;
-    // 64 (fine groups) or 128 rows per workgroup of eight wavefronts, one workgroup per CU; of four wavefronts, two per
-    // CU, where that fills the chip better (57344 rows: 448 workgroups; 20000 rows: 471 of 512 places against 157 of 256).
-    // As many workgroups per row tile as keep the launch one wave.
-    int waves = 8;
-    p->rows = b1_fine_ok ? 64 : 128;
+    // As many workgroups of eight wavefronts per row tile as keep the launch at one per CU.
+    p->nt = 512;
+    p->rows = mx_rows(b1_fine_ok);
     p->n_tiles = ceil_div(L.shape.M, p->rows);
     int64_t parts = cus / p->n_tiles > 1 ? cus / p->n_tiles : 1;
-    if (!b1_fine_ok) {
-      const int64_t parts4 = 2 * cus / p->n_tiles > 1 ? 2 * cus / p->n_tiles : 1;
-      if (p->n_tiles > cus || 10 * p->n_tiles * parts4 > 11 * 2 * p->n_tiles * parts) {
-        waves = 4;
-        parts = parts4;
-      }
-    }
-    const int64_t most = ceil_div(dv.NCP, waves);   // at least a chunk for every wavefront
+    const int64_t most = ceil_div(dv.NCP, 8);   // at least a chunk for every wavefront
     if (parts > most) parts = most;
-    p->nt = 64 * waves;
     p->units = p->n_tiles * L.NSC;
     p->blocks = p->n_tiles * parts;
     p->mx_parts = int(parts);
@@ -482,7 +479,7 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->ws_partials_off = layer_counter_bytes(L.shape.M);
     const uint64_t part_bytes = parts > 1 ? uint64_t(parts) * uint64_t(B) * uint64_t(L.Mp) * 4u : 0u;
     p->ws_image_off = round_up256(p->ws_partials_off + part_bytes);
-    p->ws_bytes = p->ws_image_off + uint64_t(dv.NCP) * uint64_t(mx_chunk_bytes(mx_instr(p->bpad)));
+    p->ws_bytes = p->ws_image_off + uint64_t(dv.NCP) * uint64_t(mx_chunk_bytes(mx_instr(p->bpad, b1_fine_ok)));
     return FLUXBIN_OK;
   }
   if (B == 1 && !force_generic && (!fine || b1_fine_ok)) {   // batch-1 kernel (mu = 8 or 4)

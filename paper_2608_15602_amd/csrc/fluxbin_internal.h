@@ -46,11 +46,13 @@ constexpr int64_t mfma_rows_lds_bytes(int64_t ncp, int64_t nblk, int bp) {
               ? ncp * 64 + nblk * 16 * (4 * bp + 4) + 64
               : mfma_rows_image_dwords(ncp, nblk, bp)) * 4;
 }
-// Block-scaled matrix-core kernel (B = 2..16): fp6 digits per activation product, instructions per 128-column chunk with
+// Block-scaled matrix-core kernel (B = 2..16), in layers with or without fine salient groups: fp6 digits per activation
+// product, instructions per 128-column chunk with
 // nbp padded batch rows (16 / nbp digits each), and bytes of a chunk's digit image (T operands of 64 lanes x 24 bytes
 // and the lanes' scale bytes).
-constexpr int kMxDigits = 6;
-constexpr int mx_instr(int nbp) { return (kMxDigits * nbp + 15) / 16; }
+constexpr int mx_digits(int nbp, bool fine) { return nbp == 16 && !fine ? 5 : 6; }
+constexpr int mx_instr(int nbp, bool fine) { return (mx_digits(nbp, fine) * nbp + 15) / 16; }
+constexpr int mx_rows(bool fine) { return fine ? 64 : 128; }   // rows per workgroup
 constexpr int64_t mx_chunk_bytes(int t) { return 1536 * t + 256 * (t > 4 ? 2 : 1); }
 // Tile counters of the split-tile reduction sit kCounterStride 32-bit words (256 bytes) apart: every workgroup
 // publishes at the end of a launch, and device-scope atomics on one memory line are serialized (densely packed

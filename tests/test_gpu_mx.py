@@ -1,6 +1,6 @@
 """The block-scaled matrix-core kernel (B = 2..16) against the fp64 oracle.
 
-Tolerance. The kernel's activation products are rounded at 2^-30 of their 32-column block's largest; everything else is
+Tolerance. The kernel's activation products are rounded at 2^-25 of their 32-column block's largest or less; everything else is
 fp32: a chunk's sum, its product with the row scale and the sum over chunks, n roundings of 2^-24 of the running value
 one after another. For random signs these add like a random walk: about sqrt(n) * 2^-24 of the result's norm with n the
 chunks (at most a few hundred here), 1e-6; the tests allow 2e-6 (fp32 output)."""
@@ -25,7 +25,7 @@ def _gpu():
 
 
 # coarse layers just past the size from which the plan takes the kernel: ragged rows and columns, several workgroups per
-# row tile; one base and more row tiles than CUs (four-wavefront workgroups); every salient chunk partly filled
+# row tile; one base and more row tiles than CUs (up to 4 rows); every salient chunk partly filled
 COARSE = [LayerSpec("mx_mu4", M=4177, N=17000, Kb=2, Ks=1, mu=4, S=700, g_r=128, g_s=700, outlier_frac=0.001, seed=91),
           LayerSpec("mx_tall_mu4", M=32801, N=4400, Kb=1, Ks=0, mu=4, S=0, g_r=4400, g_s=1, seed=92)]
 COARSE8 = LayerSpec("mx_mu8", M=5001, N=14001, Kb=2, Ks=1, mu=8, S=301, g_r=256, g_s=301, outlier_frac=0.001, seed=93)
@@ -33,7 +33,8 @@ FINE = [paper_config("mx_s8", 333, 1152, 3, 8, 128, seed=94), paper_config("mx_s
         paper_config("mx_s16_wide", 1000, 4096, 2, 16, 128, seed=96)]
 FINE_SMALL_BATCH = [paper_config("mx_s8_8M", 2050, 4224, 2, 8, 128, seed=97),
                     paper_config("mx_s16_8M", 4100, 2176, 1, 16, 128, seed=98)]
-CASES = ([(s, B) for s in COARSE for B in (2, 3, 8)] + [(COARSE8, B) for B in (5, 8)] +
+CASES = ([(COARSE[0], B) for B in (2, 3, 8, 9, 16)] + [(COARSE[1], B) for B in (2, 3, 4)] +
+         [(COARSE8, B) for B in (5, 8, 9, 16)] +
          [(s, B) for s in FINE for B in (9, 16)] + [(s, B) for s in FINE_SMALL_BATCH for B in (3, 4, 7)])
 
 
