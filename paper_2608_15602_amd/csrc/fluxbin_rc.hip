@@ -277,12 +277,16 @@ int64_t col_slices(int64_t M) {
 // are the masked columns of several rows, and x (minus the prior bases) is computed once, into an fp64 copy of those columns.
 //
 // 4096 x 4096, 2 + 2 bases, 8 salient columns per block, 10 rounds, both decompositions and the saliency search:
-// 9880 -> 992 us. Of the 23 launches over the full matrix a round pass takes 25 us (64 MB of X: 13 us at the copy rate)
-// and one with the sign search about 50 (fp64 issue); a launch over the masked columns 9 to 12 us (latency).
+// 9880 -> 899 us. Of the 23 launches over the full matrix a round pass takes 22 us (64 MB of X: 13 us at the copy rate)
+// and one with the sign search 34 (fp64 issue; 42 with every combination's error as its own sum and a select per sign);
+// a launch over the masked columns 9 to 12 us (latency). About 7 us of each pass are its start: the slices' sums, added by
+// four threads per column (one thread: 1 to 1.5 us more), and the quotients; two waves of smaller workgroups pay it twice
+// (768 or 1024 workgroups 1.2 to 1.3 times as long). Sign words and row scales through scalar loads: 25.8 and 39 us.
 // ---------------------------------------------------------------------------------------------------------------------
 
 constexpr int kRcWaves = 8;        // wavefronts of a workgroup
 constexpr int kRcMaxG = 128;       // block columns: two per lane
+constexpr int kRcParts = 64 * kRcWaves / kRcMaxG;   // threads per column where the slices' sums are added
 
 struct RcPass {
   RcArgs a;
@@ -323,6 +327,26 @@ __device__ __forceinline__ double rc_readlane(double v, int lane) {
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
+// v + v of lane ^ D, D = 16 or 32: the two registers of a swap hold the lane's and its partner's.
+template <int D>
+__device__ __forceinline__ double rc_add_swapped(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(u), hi = uint32_t(u >> 32);
+  uint64_t x, y;
+  if constexpr (D == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = (uint64_t(h[0]) << 32) | l[0];
+    y = (uint64_t(h[1]) << 32) | l[1];
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = (uint64_t(h[0]) << 32) | l[0];
+    y = (uint64_t(h[1]) << 32) | l[1];
+  }
+  return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+
 // Sums of four values over the wavefront, value lane & 3 in each lane: two exchange steps that halve the values carried,
 // then four that add over the lanes (3 + 4 additions instead of 24).
 __device__ __forceinline__ double rc_sum4(const double (&v)[4], int lane) {
@@ -332,59 +356,87 @@ __device__ __forceinline__ double rc_sum4(const double (&v)[4], int lane) {
   double s = (o2 ? b : a) + rc_dpp<0x4E>(o2 ? a : b);                       // quad_perm 2,3,0,1
   s += rc_dpp<0x124>(s);                                                    // row_ror 4
   s += rc_dpp<0x128>(s);                                                    // row_ror 8
-  s += __shfl_xor(s, 16, 64);
-  s += __shfl_xor(s, 32, 64);
-  return s;
+  return rc_add_swapped<32>(rc_add_swapped<16>(s));
 }
 
-// v with the sign of a +-1: negated where the mask's top bit is set.
-__device__ __forceinline__ double rc_flip(double v, uint32_t neg) {
-  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ (uint64_t(neg & 0x80000000u) << 32));
+// -b v for a sign b = +-1 given as a mask (b = +1: plus) or as a word with its top bit set for +1 (two instructions
+// either way; with the top bit, the shift that brings it there included).
+__device__ __forceinline__ double rc_minus(double v, bool plus) { return plus ? -v : v; }
+__device__ __forceinline__ double rc_minus(double v, uint32_t top) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, (uint64_t(uint32_t(u >> 32) ^ (top & 0x80000000u)) << 32) | uint32_t(u));
 }
 
-// Joint sign search (Prop. 3.3) for one element: the top bits of neg[k] are set where b_k = -1.
+// Joint sign search (Prop. 3.3) for one element: whether b_k = +1. The first of the 2^K combinations, bit k of c being
+// b_k = +1, with the least |x - sum b_k m_k|. Combinations c and ~c are each other's negatives exactly (rounding is
+// symmetric), and the choice is kept as wavefront masks: 12 vector instructions per element for K = 2.
 template <int K>
-__device__ __forceinline__ void rc_search(double x, const double (&m)[K], uint32_t (&neg)[K]) {
-  double best = 0.0;
-  int best_c = 0;
+__device__ __forceinline__ void rc_search(double x, const double (&m)[K], bool (&plus)[K]) {
+  constexpr int H = 1 << (K - 1);
+  double sum[H];   // combinations with b_{K-1} = -1
 #pragma unroll
-  for (int c = 0; c < (1 << K); ++c) {
-    double approx = 0.0;
+  for (int c = 0; c < H; ++c) {
+    double v = K > 1 && (c & 1) ? m[0] : -m[0];
 #pragma unroll
-    for (int k = 0; k < K; ++k) approx += ((c >> k) & 1) ? m[k] : -m[k];
-    const double err = fabs(x - approx);
-    if (c == 0 || err < best) {
-      best = err;
-      best_c = c;
-    }
+    for (int k = 1; k < K; ++k) v += ((c >> k) & 1) ? m[k] : -m[k];
+    sum[c] = v;
   }
+  double best = fabs(x - sum[0]);
 #pragma unroll
-  for (int k = 0; k < K; ++k) neg[k] = ((best_c >> k) & 1) ? 0u : 0x80000000u;
+  for (int k = 0; k < K; ++k) plus[k] = false;
+#pragma unroll
+  for (int c = 1; c < 2 * H; ++c) {
+    const double err = fabs(c < H ? x - sum[c] : x + sum[2 * H - 1 - c]);
+    const bool less = err < best;
+    best = fmin(best, err);
+#pragma unroll
+    for (int k = 0; k < K; ++k) plus[k] = ((c >> k) & 1) ? plus[k] | less : plus[k] & !less;
+  }
 }
 
 // Column scales of the lane's columns: base kprev's from the slices' sums (slice order), the others' as stored; base
 // k's are 1 in its initialization. col[c]: the lane's columns in the matrix, or -1.
 template <int K, int KB, RcMode MODE>
 __device__ __forceinline__ void rc_scales(const RcPass& p, int64_t blk, int64_t c0, int nc, const int64_t (&col)[2],
-                                          double* s_ac, double (&ac)[K][2]) {
+                                          double* s_ac, double (*s_part)[2][kRcMaxG], double (&ac)[K][2]) {
   const RcArgs& a = p.a;
-  if (p.kprev >= 0) {
-    const int t = int(threadIdx.x);
+  double stored[K][2];   // requested before the sums
+#pragma unroll
+  for (int kk = 0; kk < K; ++kk)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      stored[kk][c] = MODE != kRcScales && (MODE != kRcInit || kk < KB) && col[c] >= 0 && kk != p.kprev
+                          ? a.ac[int64_t(kk) * a.N + col[c]]
+                          : 0.0;
+  if (p.kprev >= 0) {   // a quarter of the slices per thread, then the quarters in order
+    const int t = int(threadIdx.x) & (kRcMaxG - 1), part = int(threadIdx.x) / kRcMaxG;
+    const int64_t q = (p.slices + kRcParts - 1) / kRcParts, r1 = q * part + q < p.slices ? q * part + q : p.slices;
     if (t < nc) {
       double n = 0.0, d = 0.0;
-      for (int64_t r0 = 0; r0 < p.slices; r0 += 8) {
-        double u[8], w[8];
+      for (int64_t r0 = q * part; r0 < r1; r0 += 4) {
+        double u[4], w[4];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const bool in = r0 + r < p.slices;
-          u[r] = in ? p.num_in[(r0 + r) * a.N + c0 + t] : 0.0;
-          w[r] = in ? p.den_in[(r0 + r) * a.G + blk] : 0.0;
+        for (int r = 0; r < 4; ++r) {   // unconditional: the loads are in flight together
+          const int64_t rr = r0 + r < r1 ? r0 + r : r1 - 1;
+          u[r] = p.num_in[rr * a.N + c0 + t];
+          w[r] = p.den_in[rr * a.G + blk];
         }
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          n += u[r];
-          d += w[r];
+        for (int r = 0; r < 4; ++r) {
+          n += r0 + r < r1 ? u[r] : 0.0;
+          d += r0 + r < r1 ? w[r] : 0.0;
         }
+      }
+      s_part[part][0][t] = n;
+      s_part[part][1][t] = d;
+    }
+    __syncthreads();
+    if (part == 0 && t < nc) {
+      double n = 0.0, d = 0.0;
+#pragma unroll
+      for (int k = 0; k < kRcParts; ++k) {
+        n += s_part[k][0][t];
+        d += s_part[k][1][t];
       }
       const bool in = p.nm == nullptr || rc_in(a, c0 + t);
       const double v = in ? n / (d + a.eps) : 0.0;
@@ -404,25 +456,26 @@ __device__ __forceinline__ void rc_scales(const RcPass& p, int64_t blk, int64_t 
         else if (kk == p.kprev)
           v = s_ac[col[c] - c0];
         else if (MODE != kRcInit || kk < KB)
-          v = a.ac[int64_t(kk) * a.N + col[c]];
+          v = stored[kk][c];
       }
       ac[kk][c] = v;
     }
 }
 
 // Target of base k for one element with the contributions m[kk] * b_kk of the other bases (order as rc_target).
-template <int K, int KB, RcMode MODE>
-__device__ __forceinline__ double rc_residual(double x, const double (&m)[K], const uint32_t (&neg)[K]) {
+template <int K, int KB, RcMode MODE, class Sign>
+__device__ __forceinline__ double rc_residual(double x, const double (&m)[K], const Sign (&b)[K]) {
   if constexpr (MODE == kRcInit) {
 #pragma unroll
-    for (int kk = 0; kk < KB; ++kk) x -= rc_flip(m[kk], neg[kk]);
+    for (int kk = 0; kk < KB; ++kk) x += rc_minus(m[kk], b[kk]);
     return x;
   }
-  double s = 0.0;
+  if constexpr (K == 1) return x;
+  double s = 0.0;   // minus their sum
 #pragma unroll
   for (int kk = 0; kk < K; ++kk)
-    if (kk != KB) s += rc_flip(m[kk], neg[kk]);
-  return x - s;
+    if (kk != KB) s = kk == (KB == 0 ? 1 : 0) ? rc_minus(m[kk], b[kk]) : s + rc_minus(m[kk], b[kk]);
+  return x + s;
 }
 
 // Whether a pass reads base kk's row scales / signs.
@@ -436,13 +489,16 @@ __device__ __forceinline__ constexpr bool rc_reads_signs(int kk) {
 }
 
 // The workgroup's column sums: the wavefronts' (and, with several rows per wavefront, the row groups') in a fixed order.
+// ALL: off covers every column of the block.
+template <bool ALL>
 __device__ __forceinline__ void rc_store_sums(const RcPass& p, int64_t blk, int64_t c0, int nc, const int (&off)[2],
                                               const double (&cn)[2], double cd, double (&s_sum)[kRcWaves][kRcMaxG],
                                               double (&s_den)[kRcWaves]) {
   const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63;
-  __syncthreads();
-  for (int t = lane; t < nc; t += 64) s_sum[wave][t] = 0.0;
-  __syncthreads();
+  if constexpr (!ALL) {
+    for (int t = lane; t < nc; t += 64) s_sum[wave][t] = 0.0;
+    __syncthreads();
+  }
 #pragma unroll
   for (int c = 0; c < 2; ++c)
     if (off[c] >= 0) s_sum[wave][off[c]] = cn[c];
@@ -473,7 +529,10 @@ struct RcRows {
 // requested before them.
 template <int K, int KB, RcMode MODE>
 __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
-  __shared__ double s_ac[kRcMaxG], s_sum[kRcWaves][kRcMaxG], s_den[kRcWaves];
+  __shared__ double s_ac[kRcMaxG], s_den[kRcWaves];
+  __shared__ union {
+    double sum[kRcWaves][kRcMaxG], part[kRcParts][2][kRcMaxG];
+  } sh;
   constexpr bool kUpdate = MODE != kRcSign, kSearch = MODE == kRcSign || MODE == kRcSignRound;
   const RcArgs& a = p.a;
   const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
@@ -507,7 +566,7 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
   RcRows<K> next;
   if (i < i1) load(i, next);   // while the column scales are put together
   double ac[K][2];
-  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, ac);
+  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, sh.part, ac);
   const double den = kUpdate ? wave_sum(ac[KB][0] * ac[KB][0] + ac[KB][1] * ac[KB][1]) + a.eps : 0.0;
 
   double cn[2] = {0.0, 0.0}, cd = 0.0;
@@ -515,8 +574,7 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
     const RcRows<K> r = next;
     if (i + 4 * kRcWaves < i1) load(i + 4 * kRcWaves, next);
     asm volatile("" ::: "memory");   // requested here
-    double num[4], tgt[4][2];
-    uint32_t neg[4][2];   // base KB's signs
+    double num[4], tgt[4][2];   // both times -1: minus the targets times base KB's signs
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       num[u] = 0.0;
@@ -525,26 +583,25 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
       for (int c = 0; c < 2; ++c) {
         const double x = off[c] >= 0 ? double(r.x[u][c]) : 0.0;
         double m[K];
-        uint32_t ng[K];
+        std::conditional_t<kSearch, bool, uint32_t> sign[K];
 #pragma unroll
         for (int kk = 0; kk < K; ++kk) {
           m[kk] = rc_reads_ar<KB, MODE>(kk) ? r.ar[kk][u] * ac[kk][c] : 0.0;
-          ng[kk] = rc_reads_signs<KB, MODE>(kk) ? ~(r.w[kk][u][c] << (31 - (lane & 31))) : 0u;
+          sign[kk] = rc_reads_signs<KB, MODE>(kk) ? r.w[kk][u][c] << (31 - (lane & 31)) : 0u;
         }
         if constexpr (kSearch) {
-          rc_search<K>(x, m, ng);
+          rc_search<K>(x, m, sign);
 #pragma unroll
-          for (int kk = 0; kk < K; ++kk)
-            ball[kk][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && (ng[kk] >> 31) == 0);
+          for (int kk = 0; kk < K; ++kk) ball[kk][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && sign[kk]);
         }
         if constexpr (kUpdate) {
-          tgt[u][c] = rc_residual<K, KB, MODE>(x, m, ng);
-          neg[u][c] = ng[KB];
+          const double t = rc_residual<K, KB, MODE>(x, m, sign);
           if constexpr (MODE == kRcInit) {
-            neg[u][c] = tgt[u][c] >= 0.0 ? 0u : 0x80000000u;
-            ball[KB][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && neg[u][c] == 0u);
+            sign[KB] = t >= 0.0 ? 0x80000000u : 0u;
+            ball[KB][c] = __builtin_amdgcn_ballot_w64(off[c] >= 0 && t >= 0.0);
           }
-          num[u] += rc_flip(ac[KB][c], neg[u][c]) * tgt[u][c];
+          tgt[u][c] = rc_minus(t, sign[KB]);
+          num[u] += ac[KB][c] * tgt[u][c];
         }
       }
       if ((kSearch || MODE == kRcInit) && i + u < i1 && lane < 2) {
@@ -556,18 +613,18 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass(RcPass p) {
     }
     if constexpr (kUpdate) {
       const double v = rc_sum4(num, lane) / den;
-      if (lane < 4 && i + lane < i1) a.ar[(int64_t(KB) * a.M + i + lane) * a.G + blk] = v;
+      if (lane < 4 && i + lane < i1) a.ar[(int64_t(KB) * a.M + i + lane) * a.G + blk] = -v;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         if (i + u >= i1) continue;
         const double vu = rc_readlane(v, u);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) cn[c] += rc_flip(vu, neg[u][c]) * tgt[u][c];
+        for (int c = 0; c < 2; ++c) cn[c] += vu * tgt[u][c];
         cd += vu * vu;
       }
     }
   }
-  if constexpr (kUpdate) rc_store_sums(p, blk, c0, nc, off, cn, cd, s_sum, s_den);
+  if constexpr (kUpdate) rc_store_sums<true>(p, blk, c0, nc, off, cn, cd, sh.sum, s_den);
 }
 
 // Listed columns only (and prior bases): U groups of 64 / P rows at a time, P = 8, 16, 32 or 64 lanes per row, C = 2
@@ -609,8 +666,7 @@ __device__ __forceinline__ void rc_list_rows(const RcPass& p, int64_t blk, int n
           if (rc_reads_signs<KB, MODE>(kk)) w[kk][u][c] = p.bits[kk * base_words + (blk * a.M + row[u]) * 2 + c];
       }
     }
-    double num[U], tgt[U][C];
-    uint32_t neg[U][C];
+    double num[U], tgt[U][C];   // both times -1: minus the targets times base KB's signs
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       num[u] = 0.0;
@@ -623,25 +679,25 @@ __device__ __forceinline__ void rc_list_rows(const RcPass& p, int64_t blk, int n
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         double m[K];
-        uint32_t ng[K];
+        std::conditional_t<kSearch, bool, uint32_t> sign[K];
 #pragma unroll
         for (int kk = 0; kk < K; ++kk) {
           m[kk] = rc_reads_ar<KB, MODE>(kk) ? ar[kk][u] * ac[kk][c] : 0.0;
-          ng[kk] = rc_reads_signs<KB, MODE>(kk) ? (((w[kk][u][c] >> pos) & 1u) != 0 ? 0u : 0x80000000u) : 0u;
+          sign[kk] = rc_reads_signs<KB, MODE>(kk) ? uint32_t(w[kk][u][c] >> pos) << 31 : 0u;
         }
         if constexpr (kSearch) {
-          rc_search<K>(x[u][c], m, ng);
+          rc_search<K>(x[u][c], m, sign);
 #pragma unroll
-          for (int kk = 0; kk < K; ++kk) store(kk, c, ng[kk] == 0u);
+          for (int kk = 0; kk < K; ++kk) store(kk, c, sign[kk]);
         }
         if constexpr (kUpdate) {
-          tgt[u][c] = rc_residual<K, KB, MODE>(x[u][c], m, ng);
-          neg[u][c] = ng[KB];
+          const double t = rc_residual<K, KB, MODE>(x[u][c], m, sign);
           if constexpr (MODE == kRcInit) {
-            neg[u][c] = tgt[u][c] >= 0.0 ? 0u : 0x80000000u;
-            store(KB, c, neg[u][c] == 0u);
+            sign[KB] = t >= 0.0 ? 0x80000000u : 0u;
+            store(KB, c, t >= 0.0);
           }
-          num[u] += rc_flip(ac[KB][c], neg[u][c]) * tgt[u][c];
+          tgt[u][c] = rc_minus(t, sign[KB]);
+          num[u] += ac[KB][c] * tgt[u][c];
         }
       }
     }
@@ -653,9 +709,9 @@ __device__ __forceinline__ void rc_list_rows(const RcPass& p, int64_t blk, int n
       for (int u = 0; u < U; ++u) {
         const double r = num[u] / den;
         if (!in[u]) continue;
-        if (pos == 0) a.ar[(int64_t(KB) * a.M + row[u]) * a.G + blk] = r;
+        if (pos == 0) a.ar[(int64_t(KB) * a.M + row[u]) * a.G + blk] = -r;
 #pragma unroll
-        for (int c = 0; c < C; ++c) cn[c] += rc_flip(r, neg[u][c]) * tgt[u][c];
+        for (int c = 0; c < C; ++c) cn[c] += r * tgt[u][c];
         cd += r * r;
       }
     }
@@ -664,7 +720,10 @@ __device__ __forceinline__ void rc_list_rows(const RcPass& p, int64_t blk, int n
 
 template <int K, int KB, RcMode MODE>
 __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass_list(RcPass p) {
-  __shared__ double s_ac[kRcMaxG], s_sum[kRcWaves][kRcMaxG], s_den[kRcWaves];
+  __shared__ double s_ac[kRcMaxG], s_den[kRcWaves];
+  __shared__ union {
+    double sum[kRcWaves][kRcMaxG], part[kRcParts][2][kRcMaxG];
+  } sh;
   constexpr bool kUpdate = MODE != kRcSign;
   const RcArgs& a = p.a;
   const int lane = int(threadIdx.x) & 63;
@@ -682,7 +741,7 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass_list(RcPass p) {
     col[c] = off[c] >= 0 ? c0 + off[c] : -1;
   }
   double ac[K][2];
-  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, ac);
+  rc_scales<K, KB, MODE>(p, blk, c0, nc, col, s_ac, sh.part, ac);
   double den = ac[KB][0] * ac[KB][0] + ac[KB][1] * ac[KB][1];
   for (int s = 1; s < P; s <<= 1) den += __shfl_xor(den, s, 64);
   den += a.eps;
@@ -698,17 +757,17 @@ __global__ void __launch_bounds__(64 * kRcWaves) k_rc_pass_list(RcPass p) {
       cd += __shfl_xor(cd, s, 64);
     }
     if (lane >= P) off[0] = off[1] = -1;
-    rc_store_sums(p, blk, c0, nc, off, cn, cd, s_sum, s_den);
+    rc_store_sums<false>(p, blk, c0, nc, off, cn, cd, sh.sum, s_den);
   }
 }
 
 // Only the column scales of the pass before.
 template <int K>
 __global__ void __launch_bounds__(64 * kRcWaves) k_rc_last_scales(RcPass p) {
-  __shared__ double s_ac[kRcMaxG];
+  __shared__ double s_ac[kRcMaxG], s_part[kRcParts][2][kRcMaxG];
   const int64_t blk = blockIdx.x, c0 = blk * p.a.g, none[2] = {-1, -1};
   double ac[K][2];
-  rc_scales<K, 0, kRcScales>(p, blk, c0, int(c0 + p.a.g < p.a.N ? p.a.g : p.a.N - c0), none, s_ac, ac);
+  rc_scales<K, 0, kRcScales>(p, blk, c0, int(c0 + p.a.g < p.a.N ? p.a.g : p.a.N - c0), none, s_ac, s_part, ac);
 }
 
 // The masked columns of every block (a workgroup each): their offsets, their number, and zero column scales off the mask.
