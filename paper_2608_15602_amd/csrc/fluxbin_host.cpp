@@ -452,12 +452,14 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   // (40000x8192 2+1, 313 tiles on 256 CUs: 56 -> 58; 20000x8192, 157 tiles: 31.5 -> 33.2) and, with more tiles than
   // CUs, at 5 to 8 (two bases 36000x4096 26.2 -> 28.2, 34000x3072 21.9 -> 24.0; 20000x8192 27.9 -> 26.5). At up to 4 rows
   // it is faster all the same (mu = 4: 36000x4096 24.3 -> 20.9).
-  const int64_t mx_n = ceil_div(L.shape.M, mx_rows(false)), mx_p = cus / mx_n > 1 ? cus / mx_n : 1;
-  const bool mx_full = 4 * mx_n * mx_p >= 3 * ceil_div(mx_n * mx_p, cus) * cus;
+  const auto mx_ok = [&] {
+    const int64_t n = ceil_div(L.shape.M, mx_rows(false)), w = n * (cus / n > 1 ? cus / n : 1);   // workgroups
+    return B <= 4 || (B <= 8 && n <= cus) || 4 * w >= 3 * ceil_div(w, cus) * cus;
+  };
   if (B >= 2 && B <= kMaxBatch && mx_tuning(tu) &&
       ((b1_fine_ok && (B > 8 || L.shape.M * L.shape.N >= (int64_t(1) << 19))) ||
-       (!fine && use_mfma(L, B, cus, tu) && (mx_full || B <= 4 || (B <= 8 && mx_n <= cus)) &&
-        ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(B <= 8 ? 200 : 190) * cus))) {
+       (!fine && use_mfma(L, B, cus, tu) && ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(B <= 8 ? 200 : 190) * cus &&
+        mx_ok()))) {
     p->kernel = 3;
     p->bg = B <= 2 ? 2 : (B <= 4 ? 4 : (B <= 8 ? 8 : 16));
     p->bpad = p->bg;

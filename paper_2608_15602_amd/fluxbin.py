@@ -129,7 +129,11 @@ def make_shape(M, N, Kb, Ks, mu, g_r, S, g_s) -> Shape:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        # the current stream's handle from torch's own binding: 0.3 us, against 2.7 us (a third of a small call) for
+        # building the torch.cuda.Stream object that holds it
         import torch
+        if torch.cuda.is_initialized() and hasattr(torch._C, "_cuda_getCurrentRawStream"):
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return int(stream) if not hasattr(stream, "cuda_stream") else stream.cuda_stream
 
