@@ -347,8 +347,8 @@ def small_batch_us(specs, batches, launches=40, rounds=3):
 
 
 def prefill_us(specs, batches=(64, 256), launches=6):
-    """Per-call microseconds at prefill-size batches: B > 32 runs as 32-row batch tiles (one launch each, every tile
-    reading the packed weights again), graph-timed like the small-batch figures; TFLOP-eq counts 2 B M (N + S)."""
+    """Per-call microseconds at prefill-size batches: from 48 rows on large layers one many-row launch per 512 rows,
+    else 32-row batch tiles (one launch each, every tile reading the packed weights again), graph-timed like the small-batch figures; TFLOP-eq counts 2 B M (N + S)."""
     import torch
     out = {}
     for B in batches:
