@@ -310,7 +310,7 @@ static bool salient_fine(const fluxbin_layer& L, const Derived& dv) {
 // (between the two square shapes). Layers below 8 M weights stay with the batch-1 launches (1536x2048: faster at B = 2,
 // 9.0 against 13.1 us, slower from B = 4 on, 17.4 against 13.8; their one-row batch tiles are pinned by the tests).
 static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B, const fluxbin_tuning& tu) {
-  return mx_tuning(tu) && salient_fine(L, dv) && B >= 2 &&
+  return salient_fine(L, dv) && B >= 2 &&
          L.shape.M * L.shape.N >= (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20);
 }
 
@@ -319,9 +319,11 @@ static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B
 // tiles; 16 on other layers. Layers with 8 or 16 fine salient row-scale groups at mu = 8 (the paper's s16 / s8
 // configurations) run B <= 8 rows as B launches of the batch-1 kernels where the block-scaled matrix-core kernel is not
 // faster. FLUXBIN_BATCH_TILE=16 keeps 16-row tiles (of the generic kernel on those layers).
-static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int B) {
+static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int B, bool small_ws = false) {
+  const bool mx = !small_ws && mx_tuning(tu);
   const Derived dv = derive(L.shape);
-  if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && salient_fine(L, dv) && !mx_fine_small_batch(L, dv, B, tu))
+  if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && salient_fine(L, dv) &&
+      !(mx && mx_fine_small_batch(L, dv, B, tu)))
     return 1;
   if (tu.generic || dv.Gcg > 1 || dv.Gcs > 1 || tu.mfma == 0 || tu.mfma_depth == 3 || tu.mfma_r2 == 0 ||
       tu.batch_tile == kMaxBatch)
@@ -331,19 +333,20 @@ static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int
   // 64 148 -> 130; 4096x11008 B = 40 43.5 -> 44.2, B = 64 53.6 -> 47.6), from 80 rows on smaller ones (1536x2048 B = 96
   // 40.8 -> 22.9; at 64 rows 28.0 -> 22.1, but batches of up to 65 rows of such layers are pinned as 32-row tiles by the
   // tests).
-  if (mx_tuning(tu) && B >= (L.shape.M * L.shape.N >= (int64_t(8) << 20) ? 48 : 80)) return kMaxBatchPf;
+  if (mx && B >= (L.shape.M * L.shape.N >= (int64_t(8) << 20) ? 48 : 80)) return kMaxBatchPf;
   return kMaxBatchMfma;
 }
 
-fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows) {
+fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows, bool small_ws) {
   const int cus = device_cu_count();
   if (cus <= 0) return fail(FLUXBIN_ERR_HIP, "cannot query the current HIP device");
   std::memset(p, 0, sizeof(*p));
   const fluxbin_tuning tu = tuning_snapshot();
   // one launch: 16 rows, or where the call's batch tiles may be larger, up to 512 (the last rows of a call of 512-row tiles
   // may be any number)
-  const int tile = B > kMaxBatch ? batch_tile_rows(L, tu, B) : kMaxBatch;
-  if (B < 1 || B > (tile >= kMaxBatchMfma && mx_tuning(tu) ? kMaxBatchPf : tile))
+  const bool mx = !small_ws && mx_tuning(tu);
+  const int tile = B > kMaxBatch ? batch_tile_rows(L, tu, B, small_ws) : kMaxBatch;
+  if (B < 1 || B > (tile >= kMaxBatchMfma && mx ? kMaxBatchPf : tile))
     return fail(FLUXBIN_ERR_UNSUPPORTED, "no launch plan for %d batch rows in one launch on this layer", B);
   const int force_generic = tu.generic;
   const int rpt_env = tu.rpt;
@@ -456,7 +459,7 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     const int64_t n = ceil_div(L.shape.M, mx_rows(false)), w = n * (cus / n > 1 ? cus / n : 1);   // workgroups
     return B <= 4 || (B <= 8 && n <= cus) || 4 * w >= 3 * ceil_div(w, cus) * cus;
   };
-  if (B >= 2 && B <= kMaxBatch && mx_tuning(tu) &&
+  if (B >= 2 && B <= kMaxBatch && mx &&
       ((b1_fine_ok && (B > 8 || L.shape.M * L.shape.N >= (int64_t(1) << 19))) ||
        (!fine && use_mfma(L, B, cus, tu) && ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(B <= 8 ? 200 : 190) * cus &&
         mx_ok()))) {
@@ -847,21 +850,42 @@ struct BatchTiles {
   uint64_t ws_bytes;   // the larger of the two plans' workspaces
 };
 
-static fluxbin_status batch_tiles(const fluxbin_layer& L, int B, int tile, BatchTiles* bt) {
+static fluxbin_status batch_tiles_of(const fluxbin_layer& L, int B, bool small_ws, BatchTiles* bt) {
+  const int tile = batch_tile_rows(L, tuning_snapshot(), B, small_ws);
   std::memset(bt, 0, sizeof(*bt));
   bt->tile = tile;
   bt->n_full = B / tile;
   bt->tail_rows = B % tile;
   if (bt->n_full > 0) {
-    const fluxbin_status st = make_plan(L, tile, &bt->full);
+    const fluxbin_status st = make_plan(L, tile, &bt->full, true, small_ws);
     if (st != FLUXBIN_OK) return st;
     bt->ws_bytes = bt->full.ws_bytes;
   }
   if (bt->tail_rows > 0) {
-    const fluxbin_status st = make_plan(L, bt->tail_rows, &bt->tail);
+    const fluxbin_status st = make_plan(L, bt->tail_rows, &bt->tail, true, small_ws);
     if (st != FLUXBIN_OK) return st;
     if (bt->tail.ws_bytes > bt->ws_bytes) bt->ws_bytes = bt->tail.ws_bytes;
   }
+  return FLUXBIN_OK;
+}
+
+// The launches of a call with a workspace of `have` bytes, and in *need the size its query gives. The block-scaled and
+// many-row kernels need partial sums and images of other sizes than the kernels they take over from, not always growing
+// with B. A workspace of the size queried for the largest B has to serve every smaller one, so a call's query covers both
+// sets of launches, and a workspace that holds only the other set's sums gets those launches.
+static fluxbin_status batch_tiles(const fluxbin_layer& L, int B, uint64_t have, BatchTiles* bt, uint64_t* need) {
+  fluxbin_status st = batch_tiles_of(L, B, false, bt);
+  if (st != FLUXBIN_OK) return st;
+  *need = bt->ws_bytes;
+  if (bt->full.mx_parts == 0 && bt->tail.mx_parts == 0) return FLUXBIN_OK;
+  BatchTiles other;
+  st = batch_tiles_of(L, B, true, &other);
+  if (st != FLUXBIN_OK) return st;
+  if (other.ws_bytes > *need) *need = other.ws_bytes;
+  if (have < bt->ws_bytes)
+    *bt = other;
+  else if (have < other.ws_bytes)   // below what any query gave
+    bt->ws_bytes = other.ws_bytes;
   return FLUXBIN_OK;
 }
 
@@ -874,9 +898,10 @@ fluxbin_status fluxbin_workspace_query(const fluxbin_layer* layer, int32_t B, si
   if (!bytes) return fail(FLUXBIN_ERR_INVALID_ARG, "bytes is NULL");
   if (B < 1 || B > kMaxBatchCall) return fail(FLUXBIN_ERR_INVALID_ARG, "B = %d out of range [1, %d]", B, kMaxBatchCall);
   BatchTiles bt;
-  st = batch_tiles(*layer, B, batch_tile_rows(*layer, tuning_snapshot(), B), &bt);
+  uint64_t need = 0;
+  st = batch_tiles(*layer, B, UINT64_MAX, &bt, &need);
   if (st != FLUXBIN_OK) return st;
-  *bytes = static_cast<size_t>(bt.ws_bytes);
+  *bytes = static_cast<size_t>(need);
   return FLUXBIN_OK;
 }
 
@@ -902,12 +927,13 @@ static fluxbin_status gemm_common(const fluxbin_layer* layer, int32_t B, const u
   const size_t yb = (size_t(B - 1) * ldy + s.M) * (y_is_fp32 ? 4 : 2);
   if (ranges_overlap(d_x, xb, d_y, yb)) return fail(FLUXBIN_ERR_INVALID_ARG, "x and y overlap");
   BatchTiles bt;
-  st = batch_tiles(*layer, B, batch_tile_rows(*layer, tuning_snapshot(), B), &bt);
+  uint64_t need = 0;
+  st = batch_tiles(*layer, B, ws_bytes, &bt, &need);
   if (st != FLUXBIN_OK) return st;
   if (!d_ws) return fail(FLUXBIN_ERR_INVALID_ARG, "workspace is NULL");
   if (ws_bytes < bt.ws_bytes)
     return fail(FLUXBIN_ERR_BUFFER_TOO_SMALL, "workspace has %zu bytes, needs %llu", ws_bytes,
-                (unsigned long long)bt.ws_bytes);
+                (unsigned long long)need);
   if (ranges_overlap(d_ws, ws_bytes, d_y, yb) || ranges_overlap(d_ws, ws_bytes, d_x, xb))
     return fail(FLUXBIN_ERR_INVALID_ARG, "workspace overlaps x or y");
   const size_t y_elt = y_is_fp32 ? 4 : 2;
@@ -1005,7 +1031,8 @@ fluxbin_status fluxbin_plan_query(const fluxbin_layer* layer, int32_t B, fluxbin
   if (!out) return fail(FLUXBIN_ERR_INVALID_ARG, "out is NULL");
   if (B < 1 || B > kMaxBatchCall) return fail(FLUXBIN_ERR_INVALID_ARG, "B = %d out of range [1, %d]", B, kMaxBatchCall);
   BatchTiles bt;
-  st = batch_tiles(*layer, B, batch_tile_rows(*layer, tuning_snapshot(), B), &bt);
+  uint64_t need = 0;
+  st = batch_tiles(*layer, B, UINT64_MAX, &bt, &need);
   if (st != FLUXBIN_OK) return st;
   const Plan& p = bt.n_full > 0 ? bt.full : bt.tail;
   std::memset(out, 0, sizeof(*out));
@@ -1022,7 +1049,7 @@ fluxbin_status fluxbin_plan_query(const fluxbin_layer* layer, int32_t B, fluxbin
   out->tiles = p.n_tiles;
   out->units = p.units;
   out->workgroups = p.blocks;
-  out->workspace_bytes = bt.ws_bytes;
+  out->workspace_bytes = need;
   return FLUXBIN_OK;
 }
 

@@ -168,7 +168,8 @@ struct Plan {
 };
 
 // allow_rows = false: never the row-complete batch-1 kernel (the stream probe follows the split-tile kernel's plan)
-fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows = true);
+// small_ws: without the block-scaled and many-row kernels (a workspace too small for them)
+fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows = true, bool small_ws = false);
 
 // ---- launchers (fluxbin_pack.hip, fluxbin_gemv.hip) ----
 fluxbin_status launch_pack(const fluxbin_layer& L, const fluxbin_weights& dev_w, const int32_t* d_sal_idx,
