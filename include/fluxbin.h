@@ -184,8 +184,8 @@ fluxbin_status fluxbin_layer_from_header(const void* header_host, void* d_packed
 
 /*
  * Workspace of one GEMV/GEMM call with batch B (1..8192): partial sums of output rows and one 32-bit counter per row
- * tile for split reductions, and for matrix-core launches of 16 or 32 rows the call's staged activations (one image
- * per super-chunk, rewritten by every call). Before its first use the workspace must be zero-filled
+ * tile for split reductions, and for matrix-core launches the call's staged activations (an image that every call
+ * rewrites). Before its first use the workspace must be zero-filled
  * (fluxbin_workspace_init); every call leaves the counters at zero again. Calls sharing a workspace must not overlap
  * in time.
  * The counters sit in a region of the same size for every batch size of a layer, so calls of one layer with any
