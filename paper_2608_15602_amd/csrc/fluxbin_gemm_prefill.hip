@@ -9,10 +9,11 @@
 //
 // Work decomposition. A workgroup of four wavefronts takes 256 rows x 64 batch rows and a part of the column blocks (128
 // columns of the global bases, or 128 dense salient columns): per column block the activations (16 KB) and the
-// column-scale pairs of its bases go to LDS from images that a first kernel writes once per call, requested a column
-// block ahead; then every base's chunk is one step: a 16-byte load per lane brings the chunk's 64 rows (two steps ahead),
-// an un-rotation and a 4 x 4 transpose put them into operand order, and 64 matrix instructions and 64 row-scale FMAs per
-// lane follow: 1080 cycles of matrix work, about 830 of vector work. With parts > 1 the parts' sums are added by a second
+// column-scale pairs of its bases go to LDS from images that a first kernel writes once per call, requested in the first
+// step of the column block before; every base's chunk is one step: a 16-byte load per lane brings the chunk's 64 rows (one
+// step ahead: a step takes the signs out of their registers before it requests the next), an un-rotation and a 4 x 4
+// transpose put them into operand order, and 64 matrix instructions and 64 row-scale FMAs per lane follow: 1080 cycles of
+// matrix work, about 830 of vector work. With parts > 1 the parts' sums are added by a second
 // kernel in part order: deterministic. 128 rows x 128 batch rows per workgroup was 1 to 3% slower, other instruction
 // orders (interleaved by scheduling barriers, raised wavefront priority) no faster.
 //
@@ -132,15 +133,16 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
 
   if (cb0 < cb1) {
     stage(cb0, 0);
-    Signs s0, s1;
+    Signs sg;
     int cbn = cb0, kn = 0;
-    load_signs(cbn, kn, s0);
-    advance(cbn, kn);
-    load_signs(cbn, kn, s1);
+    load_signs(cbn, kn, sg);
     for (int cb = cb0; cb < cb1; ++cb) {
       const int buf = (cb - cb0) & 1;
-      __syncthreads();   // the column block has landed, and everyone is done with the other buffer
-      if (cb + 1 < cb1) stage(cb + 1, buf ^ 1);
+      // The barrier waits for no memory operation: this wavefront's copies of the column block first (its outstanding
+      // loads but the copies are the signs used next). After it every wavefront's copies have landed, and everyone is
+      // done with the other buffer.
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
       pf_f16x8 xf[4][NB];   // [K step][16 batch rows]
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -150,12 +152,9 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
       const int nk = bases(cb);
       for (int k = 0; k < nk; ++k) {
         uint32_t w[4], rs[4];
-        sign_unrotate(s0.e, rot, w);
+        sign_unrotate(sg.e, rot, w);
         sign_transpose(w);
-        sign_broadcast(s0.rs, rs);
-        s0 = s1;
-        advance(cbn, kn);
-        load_signs(cbn, kn, s1);
+        sign_broadcast(sg.rs, rs);
         uint32_t cp[16];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -163,6 +162,10 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
 #pragma unroll
           for (int i = 0; i < 4; ++i) cp[4 * q + i] = v[i];
         }
+        // after this step's LDS reads: the compiler, which cannot tell the buffers apart, waits for copies before reads
+        if (k == 0 && cb + 1 < cb1) stage(cb + 1, buf ^ 1);
+        advance(cbn, kn);
+        load_signs(cbn, kn, sg);
 #pragma unroll
         for (int r2 = 0; r2 < 4; r2 += 2) {   // two row blocks at a time
           const uint64_t ww = (uint64_t(w[r2 + 1]) << 32) | w[r2];
