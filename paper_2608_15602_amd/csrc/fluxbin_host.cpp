@@ -342,11 +342,8 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   if (cus <= 0) return fail(FLUXBIN_ERR_HIP, "cannot query the current HIP device");
   std::memset(p, 0, sizeof(*p));
   const fluxbin_tuning tu = tuning_snapshot();
-  // one launch: 16 rows, or where the call's batch tiles may be larger, up to 512 (the last rows of a call of 512-row tiles
-  // may be any number)
   const bool mx = !small_ws && mx_tuning(tu);
-  const int tile = B > kMaxBatch ? batch_tile_rows(L, tu, B, small_ws) : kMaxBatch;
-  if (B < 1 || B > (tile >= kMaxBatchMfma && mx ? kMaxBatchPf : tile))
+  if (B < 1 || (B > kMaxBatch && batch_tile_rows(L, tu, B, small_ws) < B))
     return fail(FLUXBIN_ERR_UNSUPPORTED, "no launch plan for %d batch rows in one launch on this layer", B);
   const int force_generic = tu.generic;
   const int rpt_env = tu.rpt;
@@ -402,8 +399,7 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
                   uint64_t(mfma_rows_image_dwords(dv.NCP, dv.ncg + (dv.NCP - L.shape.Kb * dv.ncg), p->bpad)) * 4u;
     return FLUXBIN_OK;
   }
-  // many-row matrix-core kernel: calls (or the last rows of calls) of more than one small-batch launch's rows whose batch
-  // tile it is (batch_tile_rows)
+  // many-row matrix-core kernel: more than one small-batch launch's rows, where batch_tile_rows allows them in one launch
   if (B > kMaxBatchMfma) {
     p->kernel = 3;
     p->many = true;
@@ -840,33 +836,38 @@ fluxbin_status fluxbin_layer_from_header(const void* header_host, void* d_packed
 
 }  // extern "C"
 
-// Batches larger than one launch's rows (batch_tile_rows: 16 or 32) run as consecutive launches of full batch tiles
+// Batches larger than one launch's rows (batch_tile_rows: 1, 16, 32 or 512) run as consecutive launches of full batch tiles
 // (the last one with the remaining rows), each with its own launch plan, one after another on the caller's stream and
 // sharing the workspace (every launch leaves its counters at zero). Each tile reads the packed weights again: the batch
-// dimension is tiled with a fixed per-launch on-chip footprint.
+// dimension is tiled with a fixed per-launch on-chip footprint. The last rows of a call of 512-row tiles run as a call of
+// these rows alone would (fewer than the many-row kernel is chosen for: 32-row tiles), so that they get the same y.
 struct BatchTiles {
-  Plan full, tail;     // plans of a full tile and of the last tile (tail rows < tile; unused if 0)
-  int tile, n_full, tail_rows;
-  uint64_t ws_bytes;   // the larger of the two plans' workspaces
+  Plan full, mid, tail;   // plans of a full tile, of the last rows' full tiles and of the last tile (unused if 0 of them)
+  int tile, n_full, mid_tile, n_mid, tail_rows;
+  uint64_t ws_bytes;      // the largest of the plans' workspaces
 };
 
 static fluxbin_status batch_tiles_of(const fluxbin_layer& L, int B, bool small_ws, BatchTiles* bt) {
-  const int tile = batch_tile_rows(L, tuning_snapshot(), B, small_ws);
+  const fluxbin_tuning tu = tuning_snapshot();
   std::memset(bt, 0, sizeof(*bt));
-  bt->tile = tile;
-  bt->n_full = B / tile;
-  bt->tail_rows = B % tile;
-  if (bt->n_full > 0) {
-    const fluxbin_status st = make_plan(L, tile, &bt->full, true, small_ws);
-    if (st != FLUXBIN_OK) return st;
-    bt->ws_bytes = bt->full.ws_bytes;
+  bt->tile = bt->mid_tile = batch_tile_rows(L, tu, B, small_ws);
+  bt->n_full = B / bt->tile;
+  bt->tail_rows = B % bt->tile;
+  if (bt->tile == kMaxBatchPf && bt->tail_rows > 0) {
+    bt->mid_tile = batch_tile_rows(L, tu, bt->tail_rows, small_ws);
+    bt->n_mid = bt->tail_rows / bt->mid_tile;
+    bt->tail_rows %= bt->mid_tile;
   }
-  if (bt->tail_rows > 0) {
-    const fluxbin_status st = make_plan(L, bt->tail_rows, &bt->tail, true, small_ws);
-    if (st != FLUXBIN_OK) return st;
-    if (bt->tail.ws_bytes > bt->ws_bytes) bt->ws_bytes = bt->tail.ws_bytes;
-  }
-  return FLUXBIN_OK;
+  const auto plan = [&](int n, int rows, Plan* p) {
+    if (n == 0) return FLUXBIN_OK;
+    const fluxbin_status st = make_plan(L, rows, p, true, small_ws);
+    if (st == FLUXBIN_OK && p->ws_bytes > bt->ws_bytes) bt->ws_bytes = p->ws_bytes;
+    return st;
+  };
+  fluxbin_status st = plan(bt->n_full, bt->tile, &bt->full);
+  if (st == FLUXBIN_OK) st = plan(bt->n_mid, bt->mid_tile, &bt->mid);
+  if (st == FLUXBIN_OK) st = plan(bt->tail_rows, bt->tail_rows, &bt->tail);
+  return st;
 }
 
 // The launches of a call with a workspace of `have` bytes, and in *need the size its query gives. The block-scaled and
@@ -877,7 +878,7 @@ static fluxbin_status batch_tiles(const fluxbin_layer& L, int B, uint64_t have, 
   fluxbin_status st = batch_tiles_of(L, B, false, bt);
   if (st != FLUXBIN_OK) return st;
   *need = bt->ws_bytes;
-  if (bt->full.mx_parts == 0 && bt->tail.mx_parts == 0) return FLUXBIN_OK;
+  if (bt->full.mx_parts == 0 && bt->mid.mx_parts == 0 && bt->tail.mx_parts == 0) return FLUXBIN_OK;
   BatchTiles other;
   st = batch_tiles_of(L, B, true, &other);
   if (st != FLUXBIN_OK) return st;
@@ -937,13 +938,15 @@ static fluxbin_status gemm_common(const fluxbin_layer* layer, int32_t B, const u
   if (ranges_overlap(d_ws, ws_bytes, d_y, yb) || ranges_overlap(d_ws, ws_bytes, d_x, xb))
     return fail(FLUXBIN_ERR_INVALID_ARG, "workspace overlaps x or y");
   const size_t y_elt = y_is_fp32 ? 4 : 2;
-  for (int t = 0; t <= bt.n_full; ++t) {
-    const int rows = t < bt.n_full ? bt.tile : bt.tail_rows;
-    if (rows == 0) break;
-    const int64_t b0 = int64_t(t) * bt.tile;
-    st = launch_gemm(*layer, t < bt.n_full ? bt.full : bt.tail, rows, d_x + b0 * ldx, ldx,
+  const int launches = bt.n_full + bt.n_mid + (bt.tail_rows > 0 ? 1 : 0);
+  int64_t b0 = 0;
+  for (int t = 0; t < launches; ++t) {
+    const bool full = t < bt.n_full, mid = !full && t < bt.n_full + bt.n_mid;
+    const int rows = full ? bt.tile : mid ? bt.mid_tile : bt.tail_rows;
+    st = launch_gemm(*layer, full ? bt.full : mid ? bt.mid : bt.tail, rows, d_x + b0 * ldx, ldx,
                      static_cast<uint8_t*>(d_y) + size_t(b0) * size_t(ldy) * y_elt, ldy, y_is_fp32, d_ws, stream);
     if (st != FLUXBIN_OK) return st;
+    b0 += rows;
   }
   return FLUXBIN_OK;
 }
@@ -1034,7 +1037,7 @@ fluxbin_status fluxbin_plan_query(const fluxbin_layer* layer, int32_t B, fluxbin
   uint64_t need = 0;
   st = batch_tiles(*layer, B, UINT64_MAX, &bt, &need);
   if (st != FLUXBIN_OK) return st;
-  const Plan& p = bt.n_full > 0 ? bt.full : bt.tail;
+  const Plan& p = bt.n_full > 0 ? bt.full : bt.n_mid > 0 ? bt.mid : bt.tail;
   std::memset(out, 0, sizeof(*out));
   out->kernel = p.kernel;
   out->threads = p.nt;
@@ -1043,7 +1046,7 @@ fluxbin_status fluxbin_plan_query(const fluxbin_layer* layer, int32_t B, fluxbin
   out->batch_groups = p.n_groups;
   out->second_kernel_reduction = p.reduce2 ? 1 : 0;
   out->early = p.early ? 1 : 0;
-  out->batch_tiles = bt.n_full + (bt.tail_rows > 0 ? 1 : 0);
+  out->batch_tiles = bt.n_full + bt.n_mid + (bt.tail_rows > 0 ? 1 : 0);
   out->batch_tile_rows = bt.tile;
   out->workgroups_per_tile = p.kpt;
   out->tiles = p.n_tiles;

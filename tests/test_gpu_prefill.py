@@ -88,3 +88,20 @@ def test_many_rows_infinities_and_subnormals():
     L.alpha_sc[:] = sub(L.alpha_sc.shape)
     y, y_ref = run_gemm(pack_layer(L), x, out_fp32=True), oracle.gemv_dense(L, x)
     assert np.linalg.norm(y - y_ref) < 2e-6 * np.linalg.norm(y_ref) and np.abs(y_ref).max() > 0
+
+
+# the last rows of a call: fewer than a many-row call of their own has on the small layer (40, 79) and on the large one
+# (47), enough for one (88), and both below and above one small launch's rows (1, 31)
+@pytest.mark.parametrize("spec,B", [(SMALL[0], 513), (SMALL[0], 543), (SMALL[0], 552), (SMALL[0], 591), (SMALL[0], 600),
+                                    (LARGE, 559)], ids=lambda v: getattr(v, "name", str(v)))
+def test_tiles_equal_calls_of_their_rows(spec, B):
+    """Every batch tile's rows, the last ones included, are bit for bit those of a call on these rows alone."""
+    import torch
+    log(f"case tiles {spec.name} B={B}")
+    L = make_layer(spec)
+    packed = pack_layer(L)
+    x = make_activations(L, B)
+    y = run_gemm(packed, x, out_fp32=True)
+    for b0 in range(0, B, 512):
+        assert np.array_equal(y[b0:b0 + 512], run_gemm(packed, x[b0:b0 + 512], out_fp32=True)), b0
+    torch.cuda.synchronize()
