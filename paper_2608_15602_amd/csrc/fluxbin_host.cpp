@@ -303,15 +303,40 @@ static bool salient_fine(const fluxbin_layer& L, const Derived& dv) {
   return L.shape.mu == 8 && dv.Gcg == 1 && (dv.Gcs == 8 || dv.Gcs == 16);
 }
 
+// Row tiles of the block-scaled kernel and workgroups per tile: as many as keep the launch at one workgroup (of eight
+// wavefronts) per CU, with at least a chunk for every wavefront.
+static int64_t mx_grid(const fluxbin_layer& L, const Derived& dv, int64_t cus, bool fine, int64_t* parts) {
+  const int64_t tiles = ceil_div(L.shape.M, mx_rows(fine)), most = ceil_div(dv.NCP, 8);
+  *parts = cus / tiles > 1 ? cus / tiles : 1;
+  if (*parts > most) *parts = most;
+  return tiles;
+}
+
 // Layers with fine salient groups at 2 <= B <= 8: the block-scaled kernel in one launch, or B batch-1 launches. us per
 // call, batch-1 launches -> block-scaled kernel, s16 / s8: 4096x4096 B = 2 12.7 / 13.2 -> 14.6 / 14.7, B = 4 24.6 /
-// 25.6 -> 15.4 / 15.9, B = 8 48.4 / 49.2 -> 17.3 / 17.3; 5120x5120 B = 2 17.1 / 18.3 -> 16.7 / 17.3; 5120x13824 B = 2
-// 30.2 / 28.5 -> 23.4 / 25.4, B = 8 116.7 / 108.1 -> 31.2 / 32.1. So from three rows on, at two rows from 24 M weights
-// (between the two square shapes). Layers below 8 M weights stay with the batch-1 launches (1536x2048: faster at B = 2,
+// 25.6 -> 15.4 / 15.9, B = 8 48.4 / 49.2 -> 17.3 / 17.3; 5120x13824 B = 2 30.2 / 28.5 -> 23.4 / 25.4, B = 8 116.7 / 108.1
+// -> 31.2 / 32.1. Layers below 8 M weights (24 M at B = 2) stay with the batch-1 launches (1536x2048: faster at B = 2,
 // 9.0 against 13.1 us, slower from B = 4 on, 17.4 against 13.8; their one-row batch tiles are pinned by the tests).
-static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B, const fluxbin_tuning& tu) {
-  return salient_fine(L, dv) && B >= 2 &&
-         L.shape.M * L.shape.N >= (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20);
+// Above that by estimated times. The block-scaled kernel's waves of workgroups (64 rows, one workgroup per CU) each cost
+// a start and their wavefronts' turns at the chunks (eight share the chunks with one row scale, two groups of four the
+// fine ones), so it loses where a last wave is nearly empty or a row tile has few chunks: 66368x512 s8 B = 2 20.4 ->
+// 32.5, B = 3 28.1 -> 42.7; 132800x256 s16 B = 3 25.6 -> 41.4; 18432x4608 s8 (288 workgroups) B = 2 1.21 times as long;
+// while 13824x5120 (216) takes 0.79 to 0.84 of the time. Over 740 calls on 191 layers of 256 to 16640 columns the choice is
+// at most 4% slower than the batch-1 launches and keeps 95% of the block-scaled kernel's gain.
+static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B) {
+  const int64_t MN = L.shape.M * L.shape.N;
+  if (!salient_fine(L, dv) || B < 2 || MN < (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20)) return false;
+  const int64_t cus = device_cu_count();
+  if (cus <= 0) return false;   // make_plan reports it
+  int64_t parts = 1;
+  const int64_t tiles = mx_grid(L, dv, cus, true, &parts);
+  const int i = B <= 2 ? 0 : (B <= 4 ? 1 : 2);   // by padded batch rows
+  const double step[3] = {0.55, 0.75, 1.05}, fine8[3] = {1.6, 3.0, 3.7}, fine16[3] = {0.65, 0.8, 0.6};   // us
+  const double one = 3.0 + step[i] * double(ceil_div(ceil_div(dv.nfc, parts), 8)) +
+                     (dv.Gcs == 16 ? fine8 : fine16)[i] * double(ceil_div(ceil_div(dv.NCP - dv.nfc, parts), 2));
+  const double mx = 6.3 + double(ceil_div(tiles * parts, cus)) * one + (parts > 1 ? 1.3 : 0.0);
+  const double b1 = 5.25 + 0.22 * double(L.shape.Kb) * double(MN) / 8e6;   // MB of signs
+  return mx < double(B) * b1;
 }
 
 // Rows of a full batch tile (calls with more batch rows run as several launches): on layers the matrix-core kernel takes
@@ -323,7 +348,7 @@ static int batch_tile_rows(const fluxbin_layer& L, const fluxbin_tuning& tu, int
   const bool mx = !small_ws && mx_tuning(tu);
   const Derived dv = derive(L.shape);
   if (!tu.generic && tu.batch_tile != kMaxBatch && B <= 8 && salient_fine(L, dv) &&
-      !(mx && mx_fine_small_batch(L, dv, B, tu)))
+      !(mx && mx_fine_small_batch(L, dv, B)))
     return 1;
   if (tu.generic || dv.Gcg > 1 || dv.Gcs > 1 || tu.mfma == 0 || tu.mfma_depth == 3 || tu.mfma_r2 == 0 ||
       tu.batch_tile == kMaxBatch)
@@ -450,8 +475,16 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   // last wave of workgroups is mostly empty is left to the fp16 kernel, which splits the work evenly, at 9 to 16 rows
   // (40000x8192 2+1, 313 tiles on 256 CUs: 56 -> 58; 20000x8192, 157 tiles: 31.5 -> 33.2) and, with more tiles than
   // CUs, at 5 to 8 (two bases 36000x4096 26.2 -> 28.2, 34000x3072 21.9 -> 24.0; 20000x8192 27.9 -> 26.5). At up to 4 rows
-  // it is faster all the same (mu = 4: 36000x4096 24.3 -> 20.9).
+  // it is faster all the same (mu = 4: 36000x4096 24.3 -> 20.9). Layers of few chunks, of which a workgroup's eight
+  // wavefronts have fewer than two each, stay with the fp16 kernel where that leaves too many of them idle: at 3 to 8 rows
+  // below 16 chunks (fp16 kernel -> this: two bases 1048576x128, 2 chunks, B = 8 49 -> 83; 211968x256, 4, B = 4 14.6 ->
+  // 19.1; 141312x384, 6, B = 3 15.0 -> 17.9; 264960x512, 8, B = 8 32.1 -> 35.3; 176640x768, 12, B = 8 26.4 -> 28.5;
+  // 100000x896, 14, B = 4 1.05 times as long; 132480x1024, 16, 0.94 to 1.01 times), at two rows below 6 (4: 14.3 -> 15.6; 6:
+  // 0.86 to 1.01 times), at 9 to 16 rows where less than three quarters and a bit of the turns are used (2 chunks, B = 16
+  // 82 -> 97; 4 to 6 and 10 to 12 0.66 to 1.07 times; 8 and 14 0.68 to 1.0 times).
   const auto mx_ok = [&] {
+    const bool chunks = dv.NCP >= 16 || (B == 2 && dv.NCP >= 6) || (B > 8 && dv.NCP > 6 * ceil_div(dv.NCP, 8));
+    if (!chunks) return false;
     const int64_t n = ceil_div(L.shape.M, mx_rows(false)), w = n * (cus / n > 1 ? cus / n : 1);   // workgroups
     return B <= 4 || (B <= 8 && n <= cus) || 4 * w >= 3 * ceil_div(w, cus) * cus;
   };
@@ -465,13 +498,10 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->n_groups = 1;
     p->rpt = 1;
     p->depth = 2;
-    // As many workgroups of eight wavefronts per row tile as keep the launch at one per CU.
     p->nt = 512;
     p->rows = mx_rows(b1_fine_ok);
-    p->n_tiles = ceil_div(L.shape.M, p->rows);
-    int64_t parts = cus / p->n_tiles > 1 ? cus / p->n_tiles : 1;
-    const int64_t most = ceil_div(dv.NCP, 8);   // at least a chunk for every wavefront
-    if (parts > most) parts = most;
+    int64_t parts = 1;
+    p->n_tiles = mx_grid(L, dv, cus, b1_fine_ok, &parts);
     p->units = p->n_tiles * L.NSC;
     p->blocks = p->n_tiles * parts;
     p->mx_parts = int(parts);
