@@ -6,6 +6,8 @@
 // GEMV kernels read the salient refinement exactly like the global bases.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fluxbin_internal.h"
 
 namespace fluxbin {
@@ -57,17 +59,9 @@ __device__ inline int chunk_kind(const PackArgs& a, int64_t c, int64_t* k, int64
 // Row scales per chunk c and row (1: one plane; G > 1: a block of G scales per row), by the chunk's scale layout.
 __device__ inline int64_t chunk_G(const PackArgs& a, int64_t c) { return c < a.nfc ? a.Gcg : a.Gcs; }
 
-// Sub-vector held at position q of row i's 16-byte entry of a chunk with G scale groups (spc = 128/mu positions,
-// n = spc/G per group): the groups are rotated by floor(i/n) and the positions within a group by i, so that any
-// spc consecutive rows read spc different sub-vectors at every position (G = 1: (q + i) mod spc).
-__device__ inline int sub_at(int q, int64_t i, int spc, int G) {
-  const int n = spc / G;
-  const int blk = int(((q / n) + (i / n)) % G);
-  const int w = int(((q % n) + i) % n);
-  return blk * n + w;
-}
-
-// Inverse of sub_at: the position of sub-vector u.
+// Position of sub-vector u in row i's 16-byte entry of a chunk with G scale groups (spc = 128/mu positions, n = spc/G per
+// group): the groups are rotated by floor(i/n) and the positions within a group by i, so that any spc consecutive rows
+// read spc different sub-vectors at every position (G = 1: sub-vector (q + i) mod spc at position q).
 __device__ inline int pos_of(int u, int64_t i, int spc, int G) {
   const int n = spc / G;
   const int blk = int((((u / n) - (i / n)) % G + G) % G);
@@ -86,83 +80,100 @@ __device__ inline void rotate_right(uint32_t w[4], uint32_t rot) {
   for (int m = 0; m < 4; ++m) w[m] = r2 ? h[(m + 2) & 3] : h[m];
 }
 
-constexpr int kPackRows = 64, kPackChunks = 16;   // a workgroup's tile of packed entries
+// Every field of f bits (16, 32 or 64; 8 at mu = 4) of the 128 rotated right by rot < f.
+__device__ inline void rotate_fields(uint32_t w[4], int f, uint32_t rot) {
+  if (f == 64) {
+    for (int p = 0; p < 4; p += 2) {
+      const uint32_t lo = __builtin_amdgcn_alignbit(w[p + 1], w[p], rot & 31u);
+      const uint32_t hi = __builtin_amdgcn_alignbit(w[p], w[p + 1], rot & 31u);
+      w[p] = (rot & 32u) != 0 ? hi : lo;
+      w[p + 1] = (rot & 32u) != 0 ? lo : hi;
+    }
+  } else if (f == 32) {
+    for (int m = 0; m < 4; ++m) w[m] = __builtin_amdgcn_alignbit(w[m], w[m], rot);
+  } else {
+    const uint32_t low = ~0u / ((1u << f) - 1u) * ((1u << (f - rot)) - 1u);   // the f - rot low bits of every field
+    for (int m = 0; m < 4; ++m) w[m] = ((w[m] >> rot) & low) | ((w[m] << (f - rot)) & ~low);
+  }
+}
 
-// A workgroup packs 64 rows x 16 chunks: a transpose of 16-byte pieces through LDS. A wavefront reads 256 contiguous bytes
-// of a row (the tile's 16 chunks of a global base, one word per lane) and writes 1 KB runs of a chunk's rows. A salient
+constexpr int kPackRows = 64;   // rows of a workgroup's tile of packed entries
+
+// A workgroup packs 64 rows x C chunks: a transpose of 16-byte pieces through LDS. A wavefront reads 16 C contiguous bytes
+// of a row (the tile's chunks of a global base, one word per lane) and writes 1 KB runs of a chunk's rows. A salient
 // chunk's bits are gathered 64 columns at a time, a lane each, and collected by a ballot: the column indices are read
 // once per tile and the row's words come from the caches. Bound by memory: 28672 x 8192 with 3 bases + 5% (117 MB read,
-// 90 MB written) 229 -> 58 us; one thread per entry read rows 1 KB apart and salient columns one after another.
+// 90 MB written) 229 -> 58 us; one thread per entry read rows 1 KB apart and salient columns one after another. C = 16, or
+// 4 where that leaves workgroups for fewer than the CUs (a tile's salient chunks follow one another: 64 x 4096, all columns
+// salient, 4 bases, whole call 71 -> 48 us; 64 x 28672, half of them salient, 88 -> 66).
+template <int C>
 __global__ void __launch_bounds__(256) k_pack_signs(PackArgs a) {
-  __shared__ uint32_t tile[kPackRows][4 * kPackChunks + 4];   // 4 words of padding: rows on different banks
+  constexpr int LW = 4 * C, RL = 64 / LW;   // a wavefront's load: RL rows of LW words
+  __shared__ uint32_t tile[kPackRows][LW + 4];   // 4 words of padding: rows on different banks
   const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
   // the last chunks first: the salient ones, whose workgroups take longest
-  const int64_t i0 = int64_t(blockIdx.x) * kPackRows, c0 = int64_t(gridDim.y - 1 - blockIdx.y) * kPackChunks;
+  const int64_t i0 = int64_t(blockIdx.x) * kPackRows, c0 = int64_t(gridDim.y - 1 - blockIdx.y) * C;
   {
-    // global chunks: lane l takes word l & 3 of chunk c0 + l / 4
-    const int64_t c = c0 + (lane >> 2);
+    // global chunks: lane l takes word l & 3 of chunk c0 + (l mod LW) / 4, of row l / LW of a load
+    const int64_t c = c0 + (lane % LW >> 2);
     int64_t k = 0, col0 = 0;
     const bool global = c < a.NCP && chunk_kind(a, c, &k, &col0) == 0;
     const int64_t j0 = col0 + 32 * (lane & 3);
     const bool read = global && j0 < a.N;
     const uint32_t keep = a.N - j0 < 32 ? (1u << ((a.N - j0) & 31)) - 1u : ~0u;
     const uint32_t* src = a.signs + (read ? k * a.M * a.W + j0 / 32 : 0);
-    uint32_t w[kPackRows / 4];
+    uint32_t w[kPackRows / (4 * RL)];
 #pragma unroll
-    for (int r = 0; r < kPackRows / 4; ++r) {
-      const int64_t i = i0 + 4 * r + wave;
+    for (int r = 0; r < kPackRows / (4 * RL); ++r) {
+      const int64_t i = i0 + (4 * r + wave) * RL + lane / LW;
       w[r] = read && i < a.M ? src[i * a.W] & keep : 0u;
     }
 #pragma unroll
-    for (int r = 0; r < kPackRows / 4; ++r) tile[4 * r + wave][lane] = w[r];
+    for (int r = 0; r < kPackRows / (4 * RL); ++r) tile[(4 * r + wave) * RL + lane / LW][lane % LW] = w[r];
   }
   __syncthreads();
   const int64_t cs = a.ngcp > c0 ? a.ngcp : c0;
-  const int64_t ce = c0 + kPackChunks < a.NC ? c0 + kPackChunks : a.NC;
+  const int64_t ce = c0 + C < a.NC ? c0 + C : a.NC;
   for (int64_t c = cs; c < ce; ++c) {   // salient chunks of the tile
     int64_t k, col0;
     if (chunk_kind(a, c, &k, &col0) != 1) continue;
+    uint32_t w[2][kPackRows / 4];   // both halves' words in flight together
+    int32_t j[2];
+#pragma unroll
     for (int half = 0; half < 2; ++half) {
       const int64_t t = col0 + 64 * half + lane;
-      const bool in = t < a.S;
-      const int32_t j = in ? a.sal_idx[t] : 0;
-      const uint32_t* src = a.sal_signs + k * a.M * a.W + (j >> 5);
-      uint32_t w[kPackRows / 4];
+      j[half] = t < a.S ? a.sal_idx[t] : -1;
+    }
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const uint32_t* src = a.sal_signs + k * a.M * a.W + (j[half] < 0 ? 0 : j[half] >> 5);
 #pragma unroll
       for (int r = 0; r < kPackRows / 4; ++r) {
         const int64_t i = i0 + 4 * r + wave;
-        w[r] = in && i < a.M ? src[i * a.W] : 0u;
-      }
-#pragma unroll
-      for (int r = 0; r < kPackRows / 4; ++r) {
-        const uint64_t bits = __builtin_amdgcn_ballot_w64(((w[r] >> (j & 31)) & 1u) != 0);
-        if (lane < 2) tile[4 * r + wave][4 * (c - c0) + 2 * half + lane] = uint32_t(bits >> (32 * lane));
+        w[half][r] = j[half] >= 0 && i < a.M ? src[i * a.W] : 0u;
       }
     }
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int r = 0; r < kPackRows / 4; ++r) {
+        const uint64_t bits = __builtin_amdgcn_ballot_w64(((w[half][r] >> (j[half] & 31)) & 1u) != 0);
+        if (lane < 2) tile[4 * r + wave][4 * (c - c0) + 2 * half + lane] = uint32_t(bits >> (32 * lane));
+      }
   }
   __syncthreads();
   const int64_t i = i0 + lane;   // Mp is a multiple of 64: every row of the tile is written
-  for (int q = wave; q < kPackChunks && c0 + q < a.NCP; q += 4) {
+  for (int q = wave; q < C && c0 + q < a.NCP; q += 4) {
     const int64_t c = c0 + q;
     uint32_t bits[4];
     for (int m = 0; m < 4; ++m) bits[m] = tile[lane][4 * q + m];
     const int G = int(chunk_G(a, c));
     if (G == 1 || G == kChunk / a.mu) {
       rotate_right(bits, uint32_t(a.mu * i) & 127u);
-    } else {
-      uint32_t o[4] = {0u, 0u, 0u, 0u};
-      if (a.mu == 8) {
-        for (int p = 0; p < 16; ++p) {
-          const int u = sub_at(p, i, 16, G);
-          o[p >> 2] |= ((bits[u >> 2] >> (8 * (u & 3))) & 0xFFu) << (8 * (p & 3));
-        }
-      } else {
-        for (int p = 0; p < 32; ++p) {
-          const int u = sub_at(p, i, 32, G);
-          o[p >> 3] |= ((bits[u >> 3] >> (4 * (u & 7))) & 0xFu) << (4 * (p & 7));
-        }
-      }
-      for (int m = 0; m < 4; ++m) bits[m] = o[m];
+    } else {   // the groups rotated by i / n, the sub-vectors of a group by i (pos_of)
+      const int f = kChunk / G, n = f / a.mu;
+      rotate_right(bits, uint32_t((i / n) % G * f));
+      rotate_fields(bits, f, uint32_t(i % n * a.mu));
     }
     const int64_t h = a.mu == 8 ? (c & 1) ^ ((i & 31) >= 16 ? 1 : 0) : (c & 1);
     reinterpret_cast<uint4*>(a.base + a.off_signs)[((c & ~int64_t(1)) + h) * a.Mp + i] =
@@ -419,7 +430,14 @@ fluxbin_status launch_pack(const fluxbin_layer& L, const fluxbin_weights& w, con
 
   const int T = 256;
   const bool sal = d.NRP > d.Pg;
-  hipLaunchKernelGGL(k_pack_signs, dim3(unsigned(d.Mp / kPackRows), grid_for(d.NCP, kPackChunks)), dim3(T), 0, stream, a);
+  const auto signs = [&](auto chunks) {
+    constexpr int C = decltype(chunks)::value;
+    hipLaunchKernelGGL(k_pack_signs<C>, dim3(unsigned(d.Mp / kPackRows), grid_for(d.NCP, C)), dim3(T), 0, stream, a);
+  };
+  if (d.Mp / kPackRows * ceil_div(d.NCP, 16) >= device_cu_count())
+    signs(std::integral_constant<int, 16>());
+  else
+    signs(std::integral_constant<int, 4>());
   auto rscale = [&](const uint16_t* src, int64_t K, int64_t groups, int64_t nc, int64_t G, int64_t p0) {
     if (G == 1) {
       hipLaunchKernelGGL(k_pack_rscale_planes, dim3(unsigned(d.Mp / 64), grid_for(groups, 64), unsigned(K)), dim3(T), 0,
