@@ -436,16 +436,26 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->n_groups = 1;
     p->n_tiles = ceil_div(L.shape.M, p->rows);
     p->units = p->n_tiles * L.NSC;
-    // Parts per tile: two workgroups per CU are resident, so with w of them per part the launch takes ceil(w parts /
-    // places) / parts of one part's time, and each part costs a share of the reduction (28672x8192 at B = 64, w = 112:
-    // 1, 2, 4, 8 parts 220 / 133 / 113 / 115 us; at B = 256, w = 448: 347 / 372 / 347 / 361; 8192x28672 at B = 256, w =
-    // 128: 737 / 424 / 355 / 348; 4096x4096 at B = 256, w = 64: 91 / 62 / 47 / 46).
+    // Parts per tile, by the estimated time in us: two workgroups per CU are resident, a step (one base's chunk) of such
+    // a pair takes 1.5, of a workgroup alone on its CU 0.95; with several parts a second kernel (5 us) adds their sums,
+    // which cost 0.2 us per MB for the first 32 MB, 0.5 beyond them. Measured at 1, 2, 3, 4, 8 parts: 28672x8192 with 3
+    // bases + 5% B = 64 (w = 112) 202 / 127 / 127 / 115 / 117, B = 256 (w = 448) 354 / 387 / 385 / 363 / 384; 8192x28672
+    // B = 256 680 / 390 / 400 / 358 / 352; two bases 57344x512 B = 512 80 / 210 (2), 57344x8192 852 / 966 / 994 / 1024 /
+    // 1140. Few row tiles need many parts: 1024x28672 3 bases + 5% B = 48 115 at 8 parts, 42 here. Over 919 calls on 40
+    // layers the choice takes 0.87 times as long as the one without the sums' cost and at most 8 parts, at worst 1.06 times.
     const int64_t w = p->n_tiles * (p->bpad / kPfBatch), places = 2 * int64_t(cus);
     const int64_t blocks = dv.ncg + dv.ncs;
+    const double steps = double(L.shape.Kb * dv.ncg + (dv.ncs > 0 ? L.shape.Ks : 0) * dv.ncs);
     double best = 0.0;
     p->mx_parts = 1;
-    for (int parts = 1; parts <= 8 && (parts == 1 || 2 * parts <= blocks); ++parts) {
-      const double cost = double(ceil_div(w * parts, places)) / parts + 0.02 * parts;
+    for (int parts = 1; parts <= 32 && (parts == 1 || 2 * parts <= blocks); ++parts) {
+      const int64_t rest = w * parts % places;
+      const double waves = 1.5 * double(w * parts / places) + (rest == 0 ? 0.0 : (rest <= cus ? 0.95 : 1.5));
+      double cost = waves * steps / parts;
+      if (parts > 1) {
+        const double mb = 4e-6 * double(parts) * double(B) * double(L.Mp);
+        cost += 5.0 + 0.2 * mb + (mb > 32.0 ? 0.3 * (mb - 32.0) : 0.0);
+      }
       if (parts == 1 || cost < best) {
         best = cost;
         p->mx_parts = parts;

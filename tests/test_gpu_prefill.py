@@ -105,3 +105,19 @@ def test_tiles_equal_calls_of_their_rows(spec, B):
     for b0 in range(0, B, 512):
         assert np.array_equal(y[b0:b0 + 512], run_gemm(packed, x[b0:b0 + 512], out_fp32=True)), b0
     torch.cuda.synchronize()
+
+
+def test_parts_are_worth_their_sums():
+    """A layer of many rows and few columns at 512 batch rows: one workgroup per tile, because the sums of several (117 MB
+    each) would take longer to write and add than the product. Sampled rows against the oracle."""
+    from paper_2608_15602_amd import fluxbin as fb
+    spec, B = LayerSpec("pf_tall", M=57344, N=512, Kb=2, Ks=0, mu=4, S=0, g_r=128, g_s=1, seed=117), 512
+    log("case many rows, tall layer")
+    L = make_layer(spec)
+    packed = pack_layer(L)
+    info = fb.fluxbin_plan_query(packed, B)
+    assert info["workgroups"] == 224 * 8 and info["workspace_bytes"] < 4 * spec.M * B, info
+    x = make_activations(L, B)
+    rows = sample_rows(spec.M, 32, seed=B)
+    y_ref = oracle.gemv_dense(L, x, rows=rows)
+    assert np.linalg.norm(run_gemm(packed, x, out_fp32=True)[:, rows] - y_ref) < 2e-6 * np.linalg.norm(y_ref)
