@@ -183,14 +183,18 @@ fluxbin_status fluxbin_layer_from_header(const void* header_host, void* d_packed
                                          fluxbin_layer* out);
 
 /*
- * Workspace of one GEMV/GEMM call with batch B (1..8192): partial sums of output rows and one 32-bit counter per row
+ * Workspace of GEMV/GEMM calls of up to B rows (1..8192): partial sums of output rows and one 32-bit counter per row
  * tile for split reductions, and for matrix-core launches the call's staged activations (an image that every call
  * rewrites). Before its first use the workspace must be zero-filled
  * (fluxbin_workspace_init); every call leaves the counters at zero again. Calls sharing a workspace must not overlap
  * in time.
  * The counters sit in a region of the same size for every batch size of a layer, so calls of one layer with any
- * B may share one workspace (of the size queried for the largest B). A workspace used for another layer must first
+ * B may share one workspace (of the size queried for the largest B: the size does not fall as B grows, and every call
+ * gets the launches of its own workspace, the same y bit for bit). A workspace used for another layer must first
  * be zero-filled again: the other layer's partial sums may cover this layer's counters.
+ * A call whose workspace is smaller than its query's size runs, where that is enough for them, the launches of the
+ * small-batch kernels without the block-scaled and many-row forms: the same product with other rounding, usually slower,
+ * and not what fluxbin_plan_query reports. Otherwise it fails with FLUXBIN_ERR_BUFFER_TOO_SMALL.
  */
 fluxbin_status fluxbin_workspace_query(const fluxbin_layer* layer, int32_t B, size_t* bytes);
 fluxbin_status fluxbin_workspace_init(void* d_workspace, size_t bytes, hipStream_t stream);

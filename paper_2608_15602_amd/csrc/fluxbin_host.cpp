@@ -438,7 +438,8 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->units = p->n_tiles * L.NSC;
     // Parts per tile, by the estimated time in us: two workgroups per CU are resident, a step (one base's chunk) of such
     // a pair takes 1.5, of a workgroup alone on its CU 0.95; with several parts a second kernel (5 us) adds their sums,
-    // which cost 0.2 us per MB for the first 32 MB, 0.5 beyond them. Measured at 1, 2, 3, 4, 8 parts: 28672x8192 with 3
+    // which cost 0.2 us per MB for the first 32 MB, 0.5 beyond them (128 MB at most; of the padded batch rows, so that
+    // the parts, and with them the workspace, are those of the largest batch of the same padding). Measured at 1, 2, 3, 4, 8 parts: 28672x8192 with 3
     // bases + 5% B = 64 (w = 112) 202 / 127 / 127 / 115 / 117, B = 256 (w = 448) 354 / 387 / 385 / 363 / 384; 8192x28672
     // B = 256 680 / 390 / 400 / 358 / 352; two bases 57344x512 B = 512 80 / 210 (2), 57344x8192 852 / 966 / 994 / 1024 /
     // 1140. Few row tiles need many parts: 1024x28672 3 bases + 5% B = 48 115 at 8 parts, 42 here. Over 919 calls on 40
@@ -448,12 +449,13 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     const double steps = double(L.shape.Kb * dv.ncg + (dv.ncs > 0 ? L.shape.Ks : 0) * dv.ncs);
     double best = 0.0;
     p->mx_parts = 1;
-    for (int parts = 1; parts <= 32 && (parts == 1 || 2 * parts <= blocks); ++parts) {
+    const double part_mb = 4e-6 * double(p->bpad) * double(L.Mp);
+    for (int parts = 1; parts <= 32 && (parts == 1 || (2 * parts <= blocks && part_mb * parts <= 128.0)); ++parts) {
       const int64_t rest = w * parts % places;
       const double waves = 1.5 * double(w * parts / places) + (rest == 0 ? 0.0 : (rest <= cus ? 0.95 : 1.5));
       double cost = waves * steps / parts;
       if (parts > 1) {
-        const double mb = 4e-6 * double(parts) * double(B) * double(L.Mp);
+        const double mb = part_mb * parts;
         cost += 5.0 + 0.2 * mb + (mb > 32.0 ? 0.3 * (mb - 32.0) : 0.0);
       }
       if (parts == 1 || cost < best) {
@@ -910,23 +912,30 @@ static fluxbin_status batch_tiles_of(const fluxbin_layer& L, int B, bool small_w
   return st;
 }
 
-// The launches of a call with a workspace of `have` bytes, and in *need the size its query gives. The block-scaled and
-// many-row kernels need partial sums and images of other sizes than the kernels they take over from, not always growing
-// with B. A workspace of the size queried for the largest B has to serve every smaller one, so a call's query covers both
-// sets of launches, and a workspace that holds only the other set's sums gets those launches.
-static fluxbin_status batch_tiles(const fluxbin_layer& L, int B, uint64_t have, BatchTiles* bt, uint64_t* need) {
+// The launches of a call with a workspace of `have` bytes. The block-scaled and many-row kernels need partial sums and
+// images of other sizes than the kernels they take over from; a workspace that holds only the other kernels' sums (a
+// caller's own size, or one queried for fewer rows) gets those launches.
+static fluxbin_status batch_tiles(const fluxbin_layer& L, int B, uint64_t have, BatchTiles* bt) {
   fluxbin_status st = batch_tiles_of(L, B, false, bt);
-  if (st != FLUXBIN_OK) return st;
-  *need = bt->ws_bytes;
+  if (st != FLUXBIN_OK || have >= bt->ws_bytes) return st;
   if (bt->full.mx_parts == 0 && bt->mid.mx_parts == 0 && bt->tail.mx_parts == 0) return FLUXBIN_OK;
-  BatchTiles other;
-  st = batch_tiles_of(L, B, true, &other);
+  return batch_tiles_of(L, B, true, bt);
+}
+
+// Workspace of calls of up to B rows: the largest that any of them wants, so that one workspace serves them all with the
+// same launches. The sizes do not grow with B throughout, but they do between the sizes of the padded batch (1, 2, 4, 8,
+// 16, 32, and multiples of 64 up to one many-row launch), at the top of which each kernel's sums are largest.
+static fluxbin_status workspace_need(const fluxbin_layer& L, int B, uint64_t* need) {
+  BatchTiles bt;
+  fluxbin_status st = batch_tiles_of(L, B, false, &bt);
   if (st != FLUXBIN_OK) return st;
-  if (other.ws_bytes > *need) *need = other.ws_bytes;
-  if (have < bt->ws_bytes)
-    *bt = other;
-  else if (have < other.ws_bytes)   // below what any query gave
-    bt->ws_bytes = other.ws_bytes;
+  *need = bt.ws_bytes;
+  const int many = bt.tile == kMaxBatchPf ? kMaxBatchPf : 0;
+  for (int b = 1; b < B && b <= (many > 0 ? many : kMaxBatchMfma); b = b < kMaxBatchMfma ? 2 * b : (b / 64 + 1) * 64) {
+    st = batch_tiles_of(L, b, false, &bt);
+    if (st != FLUXBIN_OK) return st;
+    if (bt.ws_bytes > *need) *need = bt.ws_bytes;
+  }
   return FLUXBIN_OK;
 }
 
@@ -938,9 +947,8 @@ fluxbin_status fluxbin_workspace_query(const fluxbin_layer* layer, int32_t B, si
   if (st != FLUXBIN_OK) return st;
   if (!bytes) return fail(FLUXBIN_ERR_INVALID_ARG, "bytes is NULL");
   if (B < 1 || B > kMaxBatchCall) return fail(FLUXBIN_ERR_INVALID_ARG, "B = %d out of range [1, %d]", B, kMaxBatchCall);
-  BatchTiles bt;
   uint64_t need = 0;
-  st = batch_tiles(*layer, B, UINT64_MAX, &bt, &need);
+  st = workspace_need(*layer, B, &need);
   if (st != FLUXBIN_OK) return st;
   *bytes = static_cast<size_t>(need);
   return FLUXBIN_OK;
@@ -968,13 +976,15 @@ static fluxbin_status gemm_common(const fluxbin_layer* layer, int32_t B, const u
   const size_t yb = (size_t(B - 1) * ldy + s.M) * (y_is_fp32 ? 4 : 2);
   if (ranges_overlap(d_x, xb, d_y, yb)) return fail(FLUXBIN_ERR_INVALID_ARG, "x and y overlap");
   BatchTiles bt;
-  uint64_t need = 0;
-  st = batch_tiles(*layer, B, ws_bytes, &bt, &need);
+  st = batch_tiles(*layer, B, ws_bytes, &bt);
   if (st != FLUXBIN_OK) return st;
   if (!d_ws) return fail(FLUXBIN_ERR_INVALID_ARG, "workspace is NULL");
-  if (ws_bytes < bt.ws_bytes)
+  if (ws_bytes < bt.ws_bytes) {
+    uint64_t need = bt.ws_bytes;
+    (void)workspace_need(*layer, B, &need);
     return fail(FLUXBIN_ERR_BUFFER_TOO_SMALL, "workspace has %zu bytes, needs %llu", ws_bytes,
                 (unsigned long long)need);
+  }
   if (ranges_overlap(d_ws, ws_bytes, d_y, yb) || ranges_overlap(d_ws, ws_bytes, d_x, xb))
     return fail(FLUXBIN_ERR_INVALID_ARG, "workspace overlaps x or y");
   const size_t y_elt = y_is_fp32 ? 4 : 2;
@@ -1075,7 +1085,8 @@ fluxbin_status fluxbin_plan_query(const fluxbin_layer* layer, int32_t B, fluxbin
   if (B < 1 || B > kMaxBatchCall) return fail(FLUXBIN_ERR_INVALID_ARG, "B = %d out of range [1, %d]", B, kMaxBatchCall);
   BatchTiles bt;
   uint64_t need = 0;
-  st = batch_tiles(*layer, B, UINT64_MAX, &bt, &need);
+  st = batch_tiles_of(*layer, B, false, &bt);
+  if (st == FLUXBIN_OK) st = workspace_need(*layer, B, &need);
   if (st != FLUXBIN_OK) return st;
   const Plan& p = bt.n_full > 0 ? bt.full : bt.n_mid > 0 ? bt.mid : bt.tail;
   std::memset(out, 0, sizeof(*out));
