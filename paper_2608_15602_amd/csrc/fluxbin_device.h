@@ -32,7 +32,6 @@ struct GemmArgs {
   int32_t ngc;       // global chunks (Kb * ncg); chunks >= ngc are salient or padding
   int32_t nfc;       // first chunk with the salient chunks' row-scale layout
   int32_t Gcg, Gcs;  // row scales per chunk and row: global / salient layout (1, or 2..32 for fine groups)
-  int32_t pf_tail;   // many-row kernel: chunks from the first salient one to the end
   int32_t kpt;       // kpt > 0: workgroup b covers part b mod kpt of tile b / kpt (tile-aligned ranges); 0: the
                      // balanced split of all units (first_unit)
 };
@@ -274,9 +273,9 @@ bool launch_gemm_mx(const GemmArgs& a, int nbp, int mu, int fg, int parts, hipSt
 void launch_reduce_parts(const GemmArgs& a, int parts, hipStream_t stream);
 
 // Many-row matrix-core kernel (fluxbin_gemm_prefill.hip), layers with one row scale per chunk: kb global bases, ks salient
-// bases of ncs chunks each; workgroups of 256 rows x kPfBatch batch rows and `parts` parts of the column blocks; false if
+// bases of ncs chunks each, the first at chunk sal0; workgroups of 256 rows x kPfBatch batch rows and `parts` parts of the column blocks; false if
 // no instance exists.
-bool launch_gemm_prefill(const GemmArgs& a, int mu, int kb, int ks, int ncs, int parts, hipStream_t stream);
+bool launch_gemm_prefill(const GemmArgs& a, int mu, int kb, int ks, int ncs, int sal0, int parts, hipStream_t stream);
 
 // Row-complete batch-1 kernel for layers with few rows (fluxbin_gemv_rows.hip): 16 rows per workgroup of `waves`
 // (4, 8 or 16) wavefronts, every super-chunk of them, `depth` (2, 4 or 6) units requested ahead, fg (0, or 8 / 16 fine

@@ -32,20 +32,20 @@ typedef _Float16 pf_f16x8 __attribute__((ext_vector_type(8)));
 constexpr int NB = kPfBatch / 16;   // 16-row batch tiles of a workgroup
 constexpr int kPfTile = 1024;   // dwords of the activations of a column block and 16 batch rows
 
-// Chunk of base k of column block cb (cb < ncg: global).
-__device__ __forceinline__ int pf_chunk(const GemmArgs& a, int cb, int k, int ncs) {
-  return cb < a.ncg ? k * a.ncg + cb : a.NCP - a.pf_tail + k * ncs + (cb - a.ncg);
+// Chunk of base k of column block cb (cb < ncg: global; the first salient chunk is sal0).
+__device__ __forceinline__ int pf_chunk(const GemmArgs& a, int cb, int k, int ncs, int sal0) {
+  return cb < a.ncg ? k * a.ncg + cb : sal0 + k * ncs + (cb - a.ncg);
 }
 
 // Activation operands: dword q of lane (batch row m, group g) for K step t of a column block holds the fp16 pair
 // x[b][32 g + j], x[b][32 g + j + 16], j = 4 t + q (the columns whose sign bits one shift brings to bits 15 and 31); zero
 // for rows past B and columns without a source. One thread per (column block, 16 batch rows, t, lane); then the
 // column-scale pairs in the same order, [column block][4 bases][4 groups][16].
-__global__ void __launch_bounds__(256) k_pf_image(GemmArgs a, int ncs, int kb, int ks, int btiles, uint32_t* ximg,
-                                                  uint32_t* cimg) {
+__global__ void __launch_bounds__(256) k_pf_image(GemmArgs a, int ncs, int sal0, int kb, int ks, int btiles,
+                                                  uint32_t* ximg, uint32_t* cimg) {
   const int cb = int(blockIdx.x), t = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63, m = lane & 15, g = lane >> 4;
   const int b = int(blockIdx.y) * 16 + m;
-  const uint16_t* idx = a.xidx + pf_chunk(a, cb, 0, ncs) * kChunk + 32 * g + 4 * t;
+  const uint16_t* idx = a.xidx + pf_chunk(a, cb, 0, ncs, sal0) * kChunk + 32 * g + 4 * t;
   const uint16_t* x = a.x + int64_t(b < a.B ? b : 0) * a.ldx;
   uint32_t xi[8];
 #pragma unroll
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(256) k_pf_image(GemmArgs a, int ncs, int kb, i
     const int k = int(threadIdx.x) >> 6, e = int(threadIdx.x) & 63;   // base, 16 g + j
     uint32_t w = 0;
     if (k < (cb < a.ncg ? kb : ks)) {
-      const uint16_t* c = a.colscale + pf_chunk(a, cb, k, ncs) * kChunk + 32 * (e >> 4) + (e & 15);
+      const uint16_t* c = a.colscale + pf_chunk(a, cb, k, ncs, sal0) * kChunk + 32 * (e >> 4) + (e & 15);
       w = uint32_t(c[0]) | (uint32_t(c[16]) << 16);
     }
     cimg[cb * 256 + int(threadIdx.x)] = w;
@@ -82,8 +82,8 @@ __device__ __forceinline__ void pf_copy_1k(const uint32_t* src, uint32_t* dst, i
 }
 
 template <int MU>
-__global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, int ncs, int kb, int ks, int btiles,
-                                                         const uint32_t* ximg, const uint32_t* cimg) {
+__global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, int ncs, int sal0, int kb, int ks,
+                                                         int btiles, const uint32_t* ximg, const uint32_t* cimg) {
   __shared__ __attribute__((aligned(16))) uint32_t xs[2][NB * kPfTile];
   __shared__ __attribute__((aligned(16))) uint32_t cs[2][256];
   const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
     uint32_t rs;
   };
   auto load_signs = [&](int cb, int k, Signs& s) __attribute__((always_inline)) {
-    const int c = pf_chunk(a, cb, k, ncs);
+    const int c = pf_chunk(a, cb, k, ncs, sal0);
     const uint8_t* p = a.signs + int64_t(c & ~1) * plane_bytes + ((uint32_t(c & 1) ^ swap) ? plane_bytes : 0) + row * 16u;
     s.e = *reinterpret_cast<const sign_u32x4*>(p);
     s.rs = a.rscale[int64_t(load_uniform_i32(a.chunk_plane, c)) * a.Mp + row];
@@ -221,19 +221,21 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
 
 }  // namespace
 
-bool launch_gemm_prefill(const GemmArgs& a, int mu, int kb, int ks, int ncs, int parts, hipStream_t stream) {
+bool launch_gemm_prefill(const GemmArgs& a, int mu, int kb, int ks, int ncs, int sal0, int parts, hipStream_t stream) {
   if ((mu != 4 && mu != 8) || parts < 1) return false;
   const int ncb = a.ncg + ncs;
   const int btiles = int(ceil_div(a.B, kPfBatch)) * NB;
   uint32_t* cimg = a.img;
   uint32_t* ximg = cimg + int64_t(ncb) * 256;
-  hipLaunchKernelGGL(k_pf_image, dim3(unsigned(ncb), unsigned(btiles)), dim3(256), 0, stream, a, ncs, kb, ks, btiles, ximg,
-                     cimg);
+  hipLaunchKernelGGL(k_pf_image, dim3(unsigned(ncb), unsigned(btiles)), dim3(256), 0, stream, a, ncs, sal0, kb, ks, btiles,
+                     ximg, cimg);
   const dim3 grid(unsigned(ceil_div(a.M, 256)), unsigned(btiles / NB), unsigned(parts));
   if (mu == 8)
-    hipLaunchKernelGGL(k_gemm_prefill<8>, grid, dim3(256), 0, stream, a, parts, ncs, kb, ks, btiles, ximg, cimg);
+    hipLaunchKernelGGL(k_gemm_prefill<8>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, btiles, ximg,
+                       cimg);
   else
-    hipLaunchKernelGGL(k_gemm_prefill<4>, grid, dim3(256), 0, stream, a, parts, ncs, kb, ks, btiles, ximg, cimg);
+    hipLaunchKernelGGL(k_gemm_prefill<4>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, btiles, ximg,
+                       cimg);
   if (parts > 1) launch_reduce_parts(a, parts, stream);
   return true;
 }

@@ -1246,9 +1246,8 @@ fluxbin_status launch_gemm(const fluxbin_layer& L, const Plan& p, int B, const u
   } else if (p.kernel == 2) {
     ok = !fine && launch_gemm_batch(a, p.n_groups, p.depth, p.bg, p.reduce2, p.xv, stream);
   } else if (p.many) {
-    a.pf_tail = int32_t(d.NCP - d.ngcp);
-    ok = !fine && launch_gemm_prefill(a, int(L.shape.mu), L.shape.Kb, d.ncs > 0 ? L.shape.Ks : 0, int(d.ncs), p.mx_parts,
-                                      stream);
+    ok = !fine && launch_gemm_prefill(a, int(L.shape.mu), L.shape.Kb, d.ncs > 0 ? L.shape.Ks : 0, int(d.ncs), int(d.ngcp),
+                                      p.mx_parts, stream);
   } else if (p.mx_parts > 0) {
     ok = fg >= 0 && launch_gemm_mx(a, p.bpad, int(L.shape.mu), fg, p.mx_parts, stream);
   } else if (p.kernel == 3) {
