@@ -199,31 +199,35 @@ __global__ void k_rc_bits(RcArgs a, uint32_t* out) {
   out[e] = bits;
 }
 
-// Column saliency S_j = sum_i W_ij^2 / h_j^2: a 1024-thread workgroup per 16 columns, 64 row slices combined in a fixed
-// order. 16 columns (64-byte row segments) rather than 64: 4096 columns are then a workgroup per CU instead of 64 workgroups
-// of four row slices (4096 x 4096: 255 -> 22 us; a read of the matrix at 5 TB/s is 13 us).
-__global__ void __launch_bounds__(1024) k_saliency(const float* W, const double* h, int64_t M, int64_t N, double* S) {
-  __shared__ double s_sum[64][17];
-  const int c = threadIdx.x & 15, slice = threadIdx.x >> 4;
-  const int64_t j = int64_t(blockIdx.x) * 16 + c;
+// Column saliency S_j = sum_i W_ij^2 / h_j^2: a workgroup per C columns, SL row slices combined in a fixed order. 16
+// columns (64-byte row segments) and 64 slices rather than 64 columns and 4 slices: 4096 columns are then a workgroup per
+// CU instead of 64 workgroups (4096 x 4096: 255 -> 22 us; a read of the matrix at 5 TB/s is 13 us). Where 64-column
+// workgroups fill the CUs as well (64 columns per CU and more), they are the faster form, with 4 slices for few rows
+// (whole search in a graph, 16 columns -> 64: 64 x 65536 23.8 -> 12.8 us, 1024 x 65536 94.6 -> 50.6, 4096 x 16384 90.9 ->
+// 49.8).
+template <int C, int SL>
+__global__ void __launch_bounds__(C * SL) k_saliency(const float* W, const double* h, int64_t M, int64_t N, double* S) {
+  __shared__ double s_sum[SL][C + 1];
+  const int c = int(threadIdx.x) % C, slice = int(threadIdx.x) / C;
+  const int64_t j = int64_t(blockIdx.x) * C + c;
   double acc = 0.0;
   if (j < N) {
     int64_t i = slice;
-    for (; i + 7 * 64 < M; i += 8 * 64) {   // eight loads in flight
+    for (; i + 7 * SL < M; i += 8 * SL) {   // eight loads in flight
       float w[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) w[u] = W[(i + 64 * u) * N + j];
+      for (int u = 0; u < 8; ++u) w[u] = W[(i + SL * u) * N + j];
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc += double(w[u]) * double(w[u]);
     }
-    for (; i < M; i += 64) {
+    for (; i < M; i += SL) {
       const double w = double(W[i * N + j]);
       acc += w * w;
     }
   }
   s_sum[slice][c] = acc;
   __syncthreads();
-  for (int half = 32; half >= 1; half >>= 1) {
+  for (int half = SL / 2; half >= 1; half >>= 1) {
     if (slice < half) s_sum[slice][c] += s_sum[slice + half][c];
     __syncthreads();
   }
@@ -1078,7 +1082,15 @@ fluxbin_status fluxbin_structural_search(const float* d_W, const double* d_hinv_
   if (g > 1024) return fail(FLUXBIN_ERR_UNSUPPORTED, "group of %lld columns > 1024", (long long)g);
   if (s > g) return fail(FLUXBIN_ERR_INVALID_ARG, "s = %lld > g = %lld", (long long)s, (long long)g);
   if (M * N > (int64_t(1) << 36)) return fail(FLUXBIN_ERR_UNSUPPORTED, "matrix too large");
-  hipLaunchKernelGGL(k_saliency, dim3(grid_for(N, 16)), dim3(1024), 0, stream, d_W, d_hinv_diag, M, N, d_scores);
+  const auto saliency = [&](auto kernel, int c, int slices) {
+    hipLaunchKernelGGL(kernel, dim3(grid_for(N, c)), dim3(unsigned(c * slices)), 0, stream, d_W, d_hinv_diag, M, N, d_scores);
+  };
+  if (N < 64 * int64_t(device_cu_count()))
+    saliency(k_saliency<16, 64>, 16, 64);
+  else if (M > 256)
+    saliency(k_saliency<64, 16>, 64, 16);
+  else
+    saliency(k_saliency<64, 4>, 64, 4);
   hipLaunchKernelGGL(k_topk, dim3(unsigned((N + g - 1) / g)), dim3(1024), 0, stream, d_scores, N, g, s, d_sal_idx,
                      d_mask);
   hipError_t e = hipGetLastError();

@@ -71,3 +71,21 @@ def test_residual_of_all_columns():
     ref0 = rc.rc_decomp(W.astype(np.float64), np.ones(N, bool), K=2, T=2, g=50)
     R = W.astype(np.float64) - rc.reconstruct(ref0["B"], ref0["alpha_r"], ref0["alpha_c"], 50)
     _compare(_gpu_rc(W, 2, 2, 128, prior=prior + (50,)), rc.rc_decomp(R, np.ones(N, bool), K=2, T=2, g=128), "residual")
+
+
+@pytest.mark.parametrize("M", [1, 70, 257, 700])
+def test_structural_search_wide(M):
+    """As many columns as fill the CUs with 64-column workgroups (few and many rows), and a column fewer than that."""
+    import torch
+    from paper_2608_15602_amd import fluxbin as fb
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for N in (64 * cus - 1, 64 * cus, 64 * cus + 70):
+        log(f"case saliency {M}x{N}")
+        rng = np.random.default_rng(91)
+        W, hinv = rng.normal(size=(M, N)).astype(np.float32), rng.uniform(0.5, 2.0, size=N)
+        scores, idx, mask = fb.fluxbin_structural_search(torch.from_numpy(W).cuda(), torch.from_numpy(hinv).cuda(), 128, 8)
+        torch.cuda.synchronize()
+        want = rc.structural_search(W.astype(np.float64), hinv, 128, 8)
+        assert np.array_equal(idx.cpu().numpy().astype(np.int64), want)
+        assert np.array_equal(np.flatnonzero(mask.cpu().numpy()), want)
+        _close(scores.cpu().numpy(), rc.saliency(W.astype(np.float64), hinv), "saliency", rtol=1e-12)
