@@ -89,3 +89,37 @@ def test_structural_search_wide(M):
         assert np.array_equal(idx.cpu().numpy().astype(np.int64), want)
         assert np.array_equal(np.flatnonzero(mask.cpu().numpy()), want)
         _close(scores.cpu().numpy(), rc.saliency(W.astype(np.float64), hinv), "saliency", rtol=1e-12)
+
+
+@pytest.mark.parametrize("M,N,K,g,T,masked", [(700, 500, 3, 192, 2, False), (620, 520, 4, 256, 1, True),
+                                              (1300, 300, 2, 300, 2, True), (600, 260, 2, 129, 2, False),
+                                              (600, 260, 2, 128, 2, False), (530, 390, 4, 130, 0, True)])
+def test_general_kernels(M, N, K, g, T, masked):
+    """Blocks of more than 128 columns (and, beside them, of 128): several row slices, three and four bases, masks."""
+    log(f"case general rc M={M} N={N} K={K} g={g} T={T} mask={masked}")
+    W, _ = make_weight_matrix(M, N, seed=100 + g)
+    mask = np.ones(N, bool)
+    if masked:
+        mask[:] = np.random.default_rng(101).random(N) < 0.3
+    ref = rc.rc_decomp(W.astype(np.float64), mask, K=K, T=T, g=g)
+    _compare(_gpu_rc(W, K, T, g, mask=mask if masked else None), ref, "general")
+
+
+def test_general_kernels_residual_and_zero_eps():
+    """Prior bases (with and without a mask) in blocks of more than 128 columns, and eps = 0."""
+    import torch
+    from paper_2608_15602_amd import fluxbin as fb
+    M, N, g = 600, 500, 250
+    log("case general rc residual")
+    W, _ = make_weight_matrix(M, N, seed=102)
+    Wd, every = W.astype(np.float64), np.ones(N, bool)
+    prior = _gpu_rc(W, 2, 2, 100)
+    ref0 = rc.rc_decomp(Wd, every, K=2, T=2, g=100)
+    R = Wd - rc.reconstruct(ref0["B"], ref0["alpha_r"], ref0["alpha_c"], 100)
+    mask = np.random.default_rng(103).random(N) < 0.2
+    _compare(_gpu_rc(W, 2, 2, g, prior=prior + (100,)), rc.rc_decomp(R, every, K=2, T=2, g=g), "residual")
+    _compare(_gpu_rc(W, 3, 1, g, mask=mask, prior=prior + (100,)), rc.rc_decomp(R, mask, K=3, T=1, g=g), "masked residual")
+    for block in (128, g):
+        out = fb.fluxbin_rc_decompose(torch.from_numpy(W).cuda(), 2, 2, block, eps=0.0)
+        torch.cuda.synchronize()
+        _compare(out, rc.rc_decomp(Wd, every, K=2, T=2, g=block, eps=0.0), f"eps 0, g {block}")
