@@ -475,7 +475,11 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
   // Block-scaled matrix-core kernel. Layers with fine salient groups, whose other kernel is the generic one: at 9 to 16
   // rows always (us per call, generic -> this, s16 / s8: 128x256 15.5 -> 12.5 / 15.8 -> 15.9, 1024x1024 33.5 -> 13.7 /
   // 33.5 -> 15.9, 4096x11008 203 -> 32.7 / 197 -> 35.8), at up to 8 rows (calls of that many rows, and the last rows of
-  // larger batches) from 2^19 weights (6 rows: 512x1024 13.6 -> about 12.5, 256x384 10.6 -> about 12.5). Layers with one
+  // larger batches) from 2^19 weights (6 rows: 512x1024 13.6 -> about 12.5, 256x384 10.6 -> about 12.5). In s8 layers,
+  // whose salient chunks take twice the instructions of s16, not with few chunks and few sign bits: at 9 to 16 rows below
+  // 2^20 bits of signs and 8 chunks (one base, generic -> this: 128x256 14.9 -> 16.5, 2048x256 15.3 -> 16.5, 2048x512 0.93
+  // to 0.99 times as long; 8 chunks, 1024x384, 0.94 times), as last rows up to 2^20 bits (20 rows: 2048x512 1.08 times as
+  // long, 4096x256 1.07; 3072x384 and 5120x256 0.83). Layers with one
   // row scale per chunk, where neither the LUT batch kernel nor the row-complete matrix-core kernel is chosen, from 200
   // (at 9 to 16 rows 190) tiles of 16 rows x 128 columns per CU: its image kernel and (with several workgroups per row
   // tile) its reduction cost 5 to 9 us, its matrix part less than half of the fp16 kernel's. us per call, fp16 kernel ->
@@ -500,8 +504,13 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     const int64_t n = ceil_div(L.shape.M, mx_rows(false)), w = n * (cus / n > 1 ? cus / n : 1);   // workgroups
     return B <= 4 || (B <= 8 && n <= cus) || 4 * w >= 3 * ceil_div(w, cus) * cus;
   };
+  const auto fine_ok = [&] {
+    const int64_t MN = L.shape.M * L.shape.N, bits = MN * L.shape.Kb, line = int64_t(1) << 20;
+    if (dv.Gcs == 8) return B > 8 || 2 * MN >= line;
+    return B > 8 ? dv.NCP >= 8 || bits >= line : 2 * MN >= line && bits > line;
+  };
   if (B >= 2 && B <= kMaxBatch && mx &&
-      ((b1_fine_ok && (B > 8 || L.shape.M * L.shape.N >= (int64_t(1) << 19))) ||
+      ((b1_fine_ok && fine_ok()) ||
        (!fine && use_mfma(L, B, cus, tu) && ceil_div(L.shape.M, 16) * dv.NCP >= int64_t(B <= 8 ? 200 : 190) * cus &&
         mx_ok()))) {
     p->kernel = 3;

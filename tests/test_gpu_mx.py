@@ -75,23 +75,28 @@ def test_block_scaled_kernel(spec, B):
 FEW_COARSE = [LayerSpec("mx_few_4", M=205001, N=250, Kb=2, Ks=0, mu=8, S=0, g_r=128, g_s=1, seed=120),
               LayerSpec("mx_few_12", M=76001, N=700, Kb=2, Ks=0, mu=4, S=0, g_r=128, g_s=1, seed=121)]
 FEW_FINE = [paper_config("mx_few_s8", 66000, 512, 2, 8, 128, seed=122),
-            paper_config("mx_few_s16", 132000, 256, 1, 16, 128, seed=123)]
+            paper_config("mx_few_s16", 132000, 256, 1, 16, 128, seed=123),
+            paper_config("mx_few_s8_small", 2000, 256, 1, 8, 128, seed=124)]
 
 
-@pytest.mark.parametrize("spec,B,rows", [(FEW_COARSE[0], 3, 256), (FEW_COARSE[0], 8, 256), (FEW_COARSE[1], 5, 256), (FEW_COARSE[1], 2, 128),
-                                         (FEW_FINE[0], 2, 1), (FEW_FINE[0], 3, 1), (FEW_FINE[1], 3, 1),
-                                         (FEW_FINE[0], 8, 64), (FEW_FINE[1], 9, 64)],
+@pytest.mark.parametrize("spec,B,rows", [(FEW_COARSE[0], 3, 256), (FEW_COARSE[0], 8, 256), (FEW_COARSE[1], 5, 256),
+                                         (FEW_COARSE[1], 2, 128), (FEW_FINE[0], 2, 1), (FEW_FINE[0], 3, 1),
+                                         (FEW_FINE[1], 3, 1), (FEW_FINE[0], 8, 64), (FEW_FINE[1], 9, 64),
+                                         (FEW_FINE[2], 9, 0), (FEW_FINE[2], 21, 0)],
                          ids=lambda v: getattr(v, "name", str(v)))
 def test_tall_layers_with_few_chunks(spec, B, rows):
     """Where most of a workgroup's wavefronts would have no chunk, the kernel is slower than those it takes over from: the
-    fp16 form (256-row tiles), or one batch-1 launch per row on layers with fine salient groups (rows = 1). Sampled rows
-    against the oracle."""
+    fp16 form (256-row tiles), or on layers with fine salient groups one batch-1 launch per row (rows = 1) or the generic
+    kernel (rows = 0). Sampled rows against the oracle."""
     from paper_2608_15602_amd import fluxbin as fb
     log(f"case few chunks {spec.name} B={B}")
     L = make_layer(spec)
     packed = pack_layer(L)
     info = fb.fluxbin_plan_query(packed, B)
-    assert (info["batch_tile_rows"] if rows == 1 else info["rows_per_tile"]) == rows, info
+    if rows == 0:
+        assert info["kernel_name"] == "generic", info
+    else:
+        assert (info["batch_tile_rows"] if rows == 1 else info["rows_per_tile"]) == rows, info
     x = make_activations(L, B)
     keep = sample_rows(spec.M, 64, seed=B)
     y_ref = oracle.gemv_dense(L, x, rows=keep)
