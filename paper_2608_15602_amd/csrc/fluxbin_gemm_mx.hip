@@ -551,9 +551,14 @@ __global__ void __launch_bounds__(64 * W) k_gemm_mx(GemmArgs a, int parts) {
     const int b = e / (16 * RB), r = e - b * 16 * RB, row = row0 + r;
     float v = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < W; ++wv)
+    for (int wv = 0; wv < W; ++wv) {
+      // a wavefront's digit sums, the smallest first: their roundings stay below those of the one addition to v (added to
+      // v one by one, at two rows 64 additions instead of 8, the results were 1.03 to 1.25 times as far off)
+      float u = red[wv][16 - NBP + b][r];
 #pragma unroll
-      for (int m = 0; m < 16; m += NBP) v += red[wv][m + b][r];
+      for (int m = 16 - 2 * NBP; m >= 0; m -= NBP) u += red[wv][m + b][r];
+      v += u;
+    }
     if constexpr (FG > 0) {
 #pragma unroll
       for (int wv = 0; wv < W; wv += 4) v += red_fine[wv + b / QB][b % QB][r];
