@@ -179,6 +179,43 @@ def test_block_scaled_subnormals_and_range(which):
         assert np.linalg.norm(y[b] - y_ref[b]) < 2e-6 * np.linalg.norm(y_ref[b]), b
 
 
+@pytest.mark.parametrize("which", ["colscale", "x", "spread", "spike", "few"])
+def test_five_digit_range(which):
+    """Five digits (9 to 16 rows, one row scale per chunk) on subnormal scales and activations, activations over the whole
+    fp16 range, one column in 32 or a few columns thousands of times larger than the others: every batch row within 2e-6 of
+    the oracle, and no further off than the fp16 form, whose products are exact (1.05: the two forms' fp32 sums differ)."""
+    from paper_2608_15602_amd import fluxbin as fb
+    spec, B = COARSE8, 11
+    log(f"case five digits {which}")
+    L = make_layer(spec)
+    rng = np.random.default_rng(6)
+    x = make_activations(L, B)
+    sub = lambda shape: rng.integers(1, 1024, size=shape).astype(np.uint16)
+    half = lambda v: v.astype(np.float16).view(np.uint16)
+    if which == "colscale":
+        L.alpha_c[:] = sub(L.alpha_c.shape)
+        L.alpha_sc[:] = sub(L.alpha_sc.shape)
+    elif which == "x":
+        x = sub(x.shape) | (rng.integers(0, 2, size=x.shape).astype(np.uint16) << 15)
+    elif which == "spread":
+        x = half(rng.normal(size=x.shape) * 2.0 ** rng.uniform(-20, 14, size=x.shape))
+    else:
+        large = np.arange(spec.N) % 32 == 5 if which == "spike" else rng.random(spec.N) < 0.002
+        x = half(rng.normal(size=x.shape) * np.where(large, 4096.0, 1.0))
+    packed = pack_layer(L)
+    assert fb.fluxbin_plan_query(packed, B)["rows_per_tile"] == 128
+    rows = sample_rows(spec.M, 512, seed=7)
+    y_ref = oracle.gemv_dense(L, x, rows=rows)
+    y = run_gemm(packed, x, out_fp32=True)[:, rows]
+    with fb.tuning(mfma=1):
+        assert fb.fluxbin_plan_query(packed, B)["rows_per_tile"] == 256
+        y16 = run_gemm(packed, x, out_fp32=True)[:, rows]
+    norm = np.linalg.norm(y_ref, axis=1)
+    err, err16 = np.linalg.norm(y - y_ref, axis=1) / norm, np.linalg.norm(y16 - y_ref, axis=1) / norm
+    log(f"  five digits {err.mean():.2e} (worst row {err.max():.2e}), fp16 form {err16.mean():.2e}")
+    assert err.max() < 2e-6 and err.mean() < 1.05 * err16.mean()
+
+
 @pytest.mark.parametrize("spec,B", [(FINE_SMALL_BATCH[0], 3), (FINE_SMALL_BATCH[0], 4), (FINE_SMALL_BATCH[1], 4),
                                     (FINE_SMALL_BATCH[0], 8)], ids=lambda v: getattr(v, "name", str(v)))
 def test_no_further_off_than_batch_1(spec, B):
