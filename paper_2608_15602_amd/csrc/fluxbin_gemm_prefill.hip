@@ -17,9 +17,14 @@
 // kernel in part order: deterministic. 128 rows x 128 batch rows per workgroup was 1 to 3% slower, other instruction
 // orders (interleaved by scheduling barriers, raised wavefront priority) no faster.
 //
+// Rounding. One accumulator for all of a part's chunks, up to several hundred additions, was up to 2.2 times as far from 64
+// bits as the 32-row launches, whose workgroups take 6 to 32 chunks each. So a run of chunks (pf_run) ends in an addition to
+// the earlier runs' sums, in LDS and the registers left: no further off than those launches over nine layers (0.59 to 1.0
+// times, 1.02 on one), for 3% of the time on average (28672x8192 at B = 256 327 -> 336 us).
+//
 // us per call, 32-row launches of the small-batch kernel -> this, on one 256-CU device: 28672x8192 with 3 bases + 5%
-// B = 64 137 -> 113, B = 128 273 -> 197, B = 256 543 -> 347 (1.06 PFLOP/s; a large fp16 matrix product reaches 1.29 on
-// the same device), 8192x28672 B = 256 570 -> 348, 4096x4096 with 2 bases + 2% B = 256 146 -> 46.
+// B = 64 137 -> 112, B = 128 273 -> 192, B = 256 543 -> 336 (1.09 PFLOP/s; a large fp16 matrix product reaches 1.29 on
+// the same device), 8192x28672 B = 256 570 -> 339, 4096x4096 with 2 bases + 2% B = 256 146 -> 42.
 #include "fluxbin_device.h"
 #include "fluxbin_signs.h"
 
@@ -75,6 +80,35 @@ __global__ void __launch_bounds__(256) k_pf_image(GemmArgs a, int ncs, int sal0,
   }
 }
 
+// Roundings of a sum of n equal random terms added in runs of r whose sums are then added in turn: the number of terms in
+// the running value, summed over the additions (the variance of the result's error, in that of one term's rounding).
+int64_t pf_roundings(int64_t n, int64_t r) {
+  if (n <= r) return n * (n + 1) / 2;
+  const int64_t runs = n / r, rest = n % r;
+  return runs * (r * (r + 1) / 2) + r * (runs * (runs + 1) / 2) + (rest > 0 ? rest * (rest + 1) / 2 + n : 0);
+}
+
+// Chunks that one accumulator takes, one after another, before its sum goes to the earlier runs': the most whose roundings,
+// with those over the parts, are no more than the 32-row launches' of the small-batch kernel (workgroups of 3 to 16
+// super-chunks, three per CU, their sums added in turn) less an eighth (runs end with a column block, up to three chunks
+// late), or as many as leave the least where that cannot be.
+int pf_run(int64_t n_chunks, int64_t row_tiles, int parts) {
+  const int64_t units = row_tiles * ((n_chunks + 1) / 2);
+  int64_t per = ceil_div(units, 3 * int64_t(device_cu_count()));
+  per = per < 3 ? 3 : per > 16 ? 16 : per;
+  const int64_t limit = pf_roundings(n_chunks, 2 * per) * 7 / 8, n = ceil_div(n_chunks, parts);
+  int64_t best = n, least = -1;
+  for (int64_t r = n; r >= 4; --r) {
+    const int64_t e = parts * pf_roundings(n, r) + (parts > 1 ? n * parts * (parts + 1) / 2 : 0);
+    if (e <= limit) return int(r);
+    if (least < 0 || e < least) {
+      least = e;
+      best = r;
+    }
+  }
+  return int(best);
+}
+
 // Copies 1 KB from src (lane l's 16 bytes at src + 4 l) to dst in LDS, without registers.
 __device__ __forceinline__ void pf_copy_1k(const uint32_t* src, uint32_t* dst, int lane) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + 4 * lane),
@@ -82,10 +116,15 @@ __device__ __forceinline__ void pf_copy_1k(const uint32_t* src, uint32_t* dst, i
 }
 
 template <int MU>
-__global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, int ncs, int sal0, int kb, int ks,
+__global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, int ncs, int sal0, int kb, int ks, int run,
                                                          int btiles, const uint32_t* ximg, const uint32_t* cimg) {
+  // 78 KB of the 80 that let two workgroups share a CU: the earlier runs' sums (of which the registers left hold the rest),
+  // and the activations and column-scale pairs of two column blocks
+  constexpr int kKept = 11;   // result vectors whose earlier sums are in LDS (the other five: in registers)
+  __shared__ __attribute__((aligned(16))) sign_f32x4 sums[kKept][256];
   __shared__ __attribute__((aligned(16))) uint32_t xs[2][NB * kPfTile];
   __shared__ __attribute__((aligned(16))) uint32_t cs[2][256];
+  static_assert(sizeof(sums) + sizeof(xs) + sizeof(cs) <= 80 * 1024, "two workgroups per CU");
   const int lane = int(threadIdx.x) & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int n = lane & 15, q4 = lane >> 4;
   const int row0 = int(blockIdx.x) * 256 + 64 * wave;
@@ -131,10 +170,32 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[rb][nb] = sign_f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // The run's sums to the earlier runs' (if there are any), and back to zero.
+  sign_f32x4 sums_reg[16 - kKept];
+#pragma unroll
+  for (int e = kKept; e < 16; ++e) sums_reg[e - kKept] = sign_f32x4{0.f, 0.f, 0.f, 0.f};
+  const int tid = int(threadIdx.x);
+  auto add_earlier = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e / NB][e % NB] += e < kKept ? sums[e][tid] : sums_reg[e - kKept];
+  };
+  auto keep = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (e < kKept)
+        sums[e][tid] = acc[e / NB][e % NB];
+      else
+        sums_reg[e - kKept] = acc[e / NB][e % NB];
+      acc[e / NB][e % NB] = sign_f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  static_assert(NB == 4, "16 result vectors");
+  bool flushed = false;
+
   if (cb0 < cb1) {
     stage(cb0, 0);
     Signs sg;
-    int cbn = cb0, kn = 0;
+    int cbn = cb0, kn = 0, left = run;
     load_signs(cbn, kn, sg);
     for (int cb = cb0; cb < cb1; ++cb) {
       const int buf = (cb - cb0) & 1;
@@ -199,8 +260,16 @@ __global__ void __launch_bounds__(256, 2) k_gemm_prefill(GemmArgs a, int parts, 
           }
         }
       }
+      left -= nk;
+      if (left <= 0 && cb + 1 < cb1) {
+        if (flushed) add_earlier();
+        keep();
+        flushed = true;
+        left = run;
+      }
     }
   }
+  if (flushed) add_earlier();
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -229,13 +298,14 @@ bool launch_gemm_prefill(const GemmArgs& a, int mu, int kb, int ks, int ncs, int
   uint32_t* ximg = cimg + int64_t(ncb) * 256;
   hipLaunchKernelGGL(k_pf_image, dim3(unsigned(ncb), unsigned(btiles)), dim3(256), 0, stream, a, ncs, sal0, kb, ks, btiles,
                      ximg, cimg);
+  const int run = pf_run(int64_t(kb) * a.ncg + ks * ncs, ceil_div(a.M, 256), parts);
   const dim3 grid(unsigned(ceil_div(a.M, 256)), unsigned(btiles / NB), unsigned(parts));
   if (mu == 8)
-    hipLaunchKernelGGL(k_gemm_prefill<8>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, btiles, ximg,
-                       cimg);
+    hipLaunchKernelGGL(k_gemm_prefill<8>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, run, btiles,
+                       ximg, cimg);
   else
-    hipLaunchKernelGGL(k_gemm_prefill<4>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, btiles, ximg,
-                       cimg);
+    hipLaunchKernelGGL(k_gemm_prefill<4>, grid, dim3(256), 0, stream, a, parts, ncs, sal0, kb, ks, run, btiles,
+                       ximg, cimg);
   if (parts > 1) launch_reduce_parts(a, parts, stream);
   return true;
 }

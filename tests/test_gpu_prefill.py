@@ -121,3 +121,26 @@ def test_parts_are_worth_their_sums():
     rows = sample_rows(spec.M, 32, seed=B)
     y_ref = oracle.gemv_dense(L, x, rows=rows)
     assert np.linalg.norm(run_gemm(packed, x, out_fp32=True)[:, rows] - y_ref) < 2e-6 * np.linalg.norm(y_ref)
+
+
+@pytest.mark.parametrize("spec", [LayerSpec("pf_long", M=16640, N=8192, Kb=2, Ks=1, mu=8, S=200, g_r=128, g_s=200,
+                                            outlier_frac=0.001, seed=118),
+                                  LayerSpec("pf_odd_run", M=20001, N=3000, Kb=3, Ks=2, mu=4, S=140, g_r=128, g_s=140,
+                                            outlier_frac=0.001, seed=119)], ids=lambda s: s.name)
+def test_no_further_off_than_32_row_launches(spec):
+    """Sums of a hundred chunks and more per part: over sampled rows no further from the oracle than the 32-row launches of
+    the small-batch kernel on the same rows (3% for the spread of the two errors over the sample)."""
+    from paper_2608_15602_amd import fluxbin as fb
+    log(f"case error {spec.name}")
+    L, B = make_layer(spec), 256
+    packed = pack_layer(L)
+    x = make_activations(L, B)
+    rows = sample_rows(spec.M, 400, seed=3)
+    y_ref = oracle.gemv_dense(L, x, rows=rows)
+    y = run_gemm(packed, x, out_fp32=True)[:, rows]
+    with fb.tuning(mfma=1):
+        assert fb.fluxbin_plan_query(packed, B)["batch_tile_rows"] == 32
+        y32 = run_gemm(packed, x, out_fp32=True)[:, rows]
+    err, err32 = np.linalg.norm(y - y_ref), np.linalg.norm(y32 - y_ref)
+    log(f"  {err / np.linalg.norm(y_ref):.2e}, 32-row launches {err32 / np.linalg.norm(y_ref):.2e}")
+    assert err < 1.03 * err32
