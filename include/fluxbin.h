@@ -210,7 +210,8 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
 
 /*
  * Y[b, :] = W-hat X[b, :] for b < B (1..8192). Up to T rows are one launch, which reads every packed sign word once
- * and uses it for all its rows (batch-independent reuse of the weights, Sec. 3.2 and App. E.2); larger batches run as
+ * and uses it for all its rows (the many-row kernel once per 64 of them; batch-independent reuse of the weights, Sec.
+ * 3.2 and App. E.2); larger batches run as
  * consecutive launches of T-row batch tiles (the last with the remaining rows), each its own launch plan, one after
  * another on the stream and sharing the workspace, so rows Tt..Tt+T-1 give the same y as a call on those rows alone.
  * T = 32 on layers with one row scale per chunk (matrix-core kernel), there 512 for B >= 48 (layers of 8 M weights and
@@ -227,11 +228,13 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
  * units (the products are exact in the fp32 accumulation, as in the LUT path; the row scale is applied per 128-column
  * chunk); on layers of 2048 to 4096 rows, or of at most 8192 rows with at most 88 super-chunks (on a 256-CU device),
  * at B <= 8 the matrix-core kernel runs row-complete (every super-chunk of 16 or 32 rows in one workgroup, no split
- * reduction). Large layers at B <= 8 and layers with 8 or 16 fine salient groups at mu = 8 run the matrix-core product
- * in its block-scaled form (signs as fp4 operands; each 32-column block of x * colscale as a sum of fp6 digits that
- * leaves at most 2^-29 of the block's largest product, below the rounding of the fp32 sums). Other layers with fine
- * row-scale groups (g_r or g_s below 128) run the generic LUT kernel for B >= 2. All are deterministic; their results
- * differ only by fp32 rounding and summation order.
+ * reduction). Large layers at B <= 16 and most layers with 8 or 16 fine salient groups at mu = 8 run the matrix-core
+ * product in its block-scaled form (signs as fp4 operands; each 32-column block of x * colscale as a sum of six fp6
+ * digits, which leaves at most 2^-29 of the block's largest product, or on layers with one row scale per chunk at 9 to 16
+ * rows of five, which leaves at most 2^-24 of it, the rounding of the fp32 sums; measured, the results are no further
+ * from 64 bits than those of the other forms). Small layers with fine salient groups and few columns, and other layers
+ * with fine row-scale groups (g_r or g_s below 128), run the generic LUT kernel where they do not run batch-1 launches.
+ * All are deterministic; their results differ only by fp32 rounding and summation order.
  */
 fluxbin_status fluxbin_lut_gemm_smallbatch(const fluxbin_layer* layer, int32_t B, const uint16_t* d_x, int64_t ldx,
                                            void* d_y, int64_t ldy, int32_t y_is_fp32, void* d_workspace,
