@@ -109,6 +109,9 @@ constexpr int kPackRows = 64;   // rows of a workgroup's tile of packed entries
 template <int C>
 __global__ void __launch_bounds__(256) k_pack_signs(PackArgs a) {
   constexpr int LW = 4 * C, RL = 64 / LW;   // a wavefront's load: RL rows of LW words
+  // halves of a salient chunk requested together: both where workgroups are few; at C = 16 they would cost 14 registers and
+  // with them two of seven wavefronts per SIMD (28672 x 8192, 3 bases + 5%, whole call 98 -> 109 us)
+  constexpr int H = C == 4 ? 2 : 1;
   __shared__ uint32_t tile[kPackRows][LW + 4];   // 4 words of padding: rows on different banks
   const int lane = int(threadIdx.x) & 63, wave = int(threadIdx.x) >> 6;
   // the last chunks first: the salient ones, whose workgroups take longest
@@ -137,29 +140,31 @@ __global__ void __launch_bounds__(256) k_pack_signs(PackArgs a) {
   for (int64_t c = cs; c < ce; ++c) {   // salient chunks of the tile
     int64_t k, col0;
     if (chunk_kind(a, c, &k, &col0) != 1) continue;
-    uint32_t w[2][kPackRows / 4];   // both halves' words in flight together
-    int32_t j[2];
+    for (int half0 = 0; half0 < 2; half0 += H) {
+      uint32_t w[H][kPackRows / 4];   // H halves' words in flight together
+      int32_t j[H];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int64_t t = col0 + 64 * half + lane;
-      j[half] = t < a.S ? a.sal_idx[t] : -1;
-    }
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const uint32_t* src = a.sal_signs + k * a.M * a.W + (j[half] < 0 ? 0 : j[half] >> 5);
-#pragma unroll
-      for (int r = 0; r < kPackRows / 4; ++r) {
-        const int64_t i = i0 + 4 * r + wave;
-        w[half][r] = j[half] >= 0 && i < a.M ? src[i * a.W] : 0u;
+      for (int h = 0; h < H; ++h) {
+        const int64_t t = col0 + 64 * (half0 + h) + lane;
+        j[h] = t < a.S ? a.sal_idx[t] : -1;
       }
-    }
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+      for (int h = 0; h < H; ++h) {
+        const uint32_t* src = a.sal_signs + k * a.M * a.W + (j[h] < 0 ? 0 : j[h] >> 5);
 #pragma unroll
-      for (int r = 0; r < kPackRows / 4; ++r) {
-        const uint64_t bits = __builtin_amdgcn_ballot_w64(((w[half][r] >> (j[half] & 31)) & 1u) != 0);
-        if (lane < 2) tile[4 * r + wave][4 * (c - c0) + 2 * half + lane] = uint32_t(bits >> (32 * lane));
+        for (int r = 0; r < kPackRows / 4; ++r) {
+          const int64_t i = i0 + 4 * r + wave;
+          w[h][r] = j[h] >= 0 && i < a.M ? src[i * a.W] : 0u;
+        }
       }
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int r = 0; r < kPackRows / 4; ++r) {
+          const uint64_t bits = __builtin_amdgcn_ballot_w64(((w[h][r] >> (j[h] & 31)) & 1u) != 0);
+          if (lane < 2) tile[4 * r + wave][4 * (c - c0) + 2 * (half0 + h) + lane] = uint32_t(bits >> (32 * lane));
+        }
+    }
   }
   __syncthreads();
   const int64_t i = i0 + lane;   // Mp is a multiple of 64: every row of the tile is written
