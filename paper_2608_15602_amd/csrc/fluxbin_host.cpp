@@ -317,25 +317,37 @@ static int64_t mx_grid(const fluxbin_layer& L, const Derived& dv, int64_t cus, b
 // 25.6 -> 15.4 / 15.9, B = 8 48.4 / 49.2 -> 17.3 / 17.3; 5120x13824 B = 2 30.2 / 28.5 -> 23.4 / 25.4, B = 8 116.7 / 108.1
 // -> 31.2 / 32.1. Layers below 8 M weights (24 M at B = 2) stay with the batch-1 launches (1536x2048: faster at B = 2,
 // 9.0 against 13.1 us, slower from B = 4 on, 17.4 against 13.8; their one-row batch tiles are pinned by the tests).
-// Above that by estimated times. The block-scaled kernel's waves of workgroups (64 rows, one workgroup per CU) each cost
-// a start and their wavefronts' turns at the chunks (eight share the chunks with one row scale, two groups of four the
-// fine ones), so it loses where a last wave is nearly empty or a row tile has few chunks: 66368x512 s8 B = 2 20.4 ->
-// 32.5, B = 3 28.1 -> 42.7; 132800x256 s16 B = 3 25.6 -> 41.4; 18432x4608 s8 (288 workgroups) B = 2 1.21 times as long;
-// while 13824x5120 (216) takes 0.79 to 0.84 of the time. Over 740 calls on 191 layers of 256 to 16640 columns the choice is
-// at most 4% slower than the batch-1 launches and keeps 95% of the block-scaled kernel's gain.
+// Above that by estimated times (us, fitted to 852 calls on 90 layers of 256 to 28672 columns and up to 80000 rows, each
+// form timed on every one, their standard deviation 5 to 9%). Block-scaled kernel: a start, a wave of workgroups (64 rows,
+// one workgroup per CU) after the other, of their wavefronts' turns at the chunks (eight share those with one row scale,
+// two groups of four the fine ones). A batch-1 launch: a start; row-complete plans then the super-chunks of 16 rows, the
+// others the most units that one workgroup takes, the row scales' MB and the sums of a split tile. So the batch-1 launches
+// win where a last wave is nearly empty or a row tile has few chunks (66368x512 s8 B = 2 20.4 -> 32.5, B = 3 28.1 -> 42.7;
+// 132800x256 s16 B = 3 25.6 -> 41.4; 18432x4608 s8, 288 workgroups, B = 2 1.24 times as long), the block-scaled kernel
+// elsewhere (B = 3 2208x23808 s16, 4 bases, 62.0 -> 34.3; B = 2 5120x13824 s16 27.5 -> 20.1). The choice takes 1.003 times
+// as long as the better form of each call.
 static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B) {
   const int64_t MN = L.shape.M * L.shape.N;
   if (!salient_fine(L, dv) || B < 2 || MN < (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20)) return false;
   const int64_t cus = device_cu_count();
-  if (cus <= 0) return false;   // make_plan reports it
+  Plan b1p;
+  if (cus <= 0 || make_plan(L, 1, &b1p) != FLUXBIN_OK) return false;   // the calls' own plans report it
+  double b1;
+  if (b1p.kernel == 4) {
+    b1 = 4.1 + double(b1p.rows / 16) * (0.052 * double(L.NSC) - 0.38);
+  } else {
+    const bool big = b1p.nt == 1024;
+    const int64_t places = cus * (big ? 1 : 2), steps = ceil_div(b1p.units, b1p.blocks < places ? b1p.blocks : places);
+    b1 = (big ? 5.1 + 1.6 * double(steps) : 4.2 + 1.3 * double(steps)) +
+         (big ? 0.26e-6 : 0.45e-6) * 2.0 * double(L.NRP * L.Mp) + 0.07 * double(L.NSC) / double(steps);
+  }
   int64_t parts = 1;
   const int64_t tiles = mx_grid(L, dv, cus, true, &parts);
   const int i = B <= 2 ? 0 : (B <= 4 ? 1 : 2);   // by padded batch rows
-  const double step[3] = {0.55, 0.75, 1.05}, fine8[3] = {1.6, 3.0, 3.7}, fine16[3] = {0.65, 0.8, 0.6};   // us
-  const double one = 3.0 + step[i] * double(ceil_div(ceil_div(dv.nfc, parts), 8)) +
-                     (dv.Gcs == 16 ? fine8 : fine16)[i] * double(ceil_div(ceil_div(dv.NCP - dv.nfc, parts), 2));
-  const double mx = 6.3 + double(ceil_div(tiles * parts, cus)) * one + (parts > 1 ? 1.3 : 0.0);
-  const double b1 = 5.25 + 0.22 * double(L.shape.Kb) * double(MN) / 8e6;   // MB of signs
+  const double step[3] = {0.53, 0.62, 0.79}, g16[3] = {1.65, 3.1, 3.85}, g8[3] = {1.05, 1.4, 2.0};
+  const double wave = 2.7 + step[i] * double(ceil_div(ceil_div(dv.nfc, parts), 8)) +
+                      (dv.Gcs == 16 ? g16 : g8)[i] * double(ceil_div(ceil_div(dv.NCP - dv.nfc, parts), 2));
+  const double mx = (parts > 1 ? 8.0 : 5.8) + double(ceil_div(tiles * parts, cus)) * wave;
   return mx < double(B) * b1;
 }
 
@@ -437,13 +449,15 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     p->n_tiles = ceil_div(L.shape.M, p->rows);
     p->units = p->n_tiles * L.NSC;
     // Parts per tile, by the estimated time in us: two workgroups per CU are resident, a step (one base's chunk) of such
-    // a pair takes 1.5, of a workgroup alone on its CU 0.95; with several parts a second kernel (5 us) adds their sums,
-    // which cost 0.2 us per MB for the first 32 MB, 0.5 beyond them (128 MB at most; of the padded batch rows, so that
-    // the parts, and with them the workspace, are those of the largest batch of the same padding). Measured at 1, 2, 3, 4, 8 parts: 28672x8192 with 3
-    // bases + 5% B = 64 (w = 112) 202 / 127 / 127 / 115 / 117, B = 256 (w = 448) 354 / 387 / 385 / 363 / 384; 8192x28672
-    // B = 256 680 / 390 / 400 / 358 / 352; two bases 57344x512 B = 512 80 / 210 (2), 57344x8192 852 / 966 / 994 / 1024 /
-    // 1140. Few row tiles need many parts: 1024x28672 3 bases + 5% B = 48 115 at 8 parts, 42 here. Over 919 calls on 40
-    // layers the choice takes 0.87 times as long as the one without the sums' cost and at most 8 parts, at worst 1.06 times.
+    // a pair takes 1.5, of a workgroup alone on its CU 0.95, and each column block's barrier and operand loads 0.4 more;
+    // with several parts a second kernel (2 us) adds their sums, which cost 0.2 us per MB for the first 32 MB, 0.5 beyond
+    // them (128 MB at most; of the padded batch rows, so that the parts, and with them the workspace, are those of the
+    // largest batch of the same padding). Measured at 1, 2, 3, 4, 8 parts: 28672x8192 with 3 bases + 5% B = 64 (w = 112)
+    // 202 / 127 / 127 / 115 / 117, B = 256 (w = 448) 354 / 387 / 385 / 363 / 384; 8192x28672 B = 256 680 / 390 / 400 / 358
+    // / 352; two bases 57344x512 B = 512 80 / 210 (2), 57344x8192 852 / 966 / 994 / 1024 / 1140. Few row tiles need many
+    // parts: 1024x28672 3 bases + 5% B = 48 115 at 8 parts, 42 here. Layers of few chunks too: 1920x896 one base + 6%, B =
+    // 100 21.2 / 17.2 / 15.9 / 14.9 (4), 296x471 2 + 1 B = 128 20.7 / 16.5. Over 60 layers of up to 60 M weights the
+    // choice takes 1.02 times as long as the best of eleven numbers of parts.
     const int64_t w = p->n_tiles * (p->bpad / kPfBatch), places = 2 * int64_t(cus);
     const int64_t blocks = dv.ncg + dv.ncs;
     const double steps = double(L.shape.Kb * dv.ncg + (dv.ncs > 0 ? L.shape.Ks : 0) * dv.ncs);
@@ -453,10 +467,10 @@ fluxbin_status make_plan(const fluxbin_layer& L, int B, Plan* p, bool allow_rows
     for (int parts = 1; parts <= 32 && (parts == 1 || (2 * parts <= blocks && part_mb * parts <= 128.0)); ++parts) {
       const int64_t rest = w * parts % places;
       const double waves = 1.5 * double(w * parts / places) + (rest == 0 ? 0.0 : (rest <= cus ? 0.95 : 1.5));
-      double cost = waves * steps / parts;
+      double cost = (waves * steps + 0.4 * double(ceil_div(w * parts, places) * blocks)) / parts;
       if (parts > 1) {
         const double mb = part_mb * parts;
-        cost += 5.0 + 0.2 * mb + (mb > 32.0 ? 0.3 * (mb - 32.0) : 0.0);
+        cost += 2.0 + 0.2 * mb + (mb > 32.0 ? 0.3 * (mb - 32.0) : 0.0);
       }
       if (parts == 1 || cost < best) {
         best = cost;

@@ -79,17 +79,21 @@ FEW_COARSE = [LayerSpec("mx_few_4", M=205001, N=250, Kb=2, Ks=0, mu=8, S=0, g_r=
 FEW_FINE = [paper_config("mx_few_s8", 66000, 512, 2, 8, 128, seed=122),
             paper_config("mx_few_s16", 132000, 256, 1, 16, 128, seed=123),
             paper_config("mx_few_s8_small", 2000, 256, 1, 8, 128, seed=124)]
+# layers of enough chunks, where it is 1.3 to 1.4 times as fast as batch-1 launches at two rows
+MANY_FINE = [paper_config("mx_many_s8", 14770, 1792, 4, 8, 128, seed=125),
+             paper_config("mx_many_s8_wide", 2208, 12160, 4, 8, 128, seed=126)]
 
 
 @pytest.mark.parametrize("spec,B,rows", [(FEW_COARSE[0], 3, 256), (FEW_COARSE[0], 8, 256), (FEW_COARSE[1], 5, 256),
                                          (FEW_COARSE[1], 2, 128), (FEW_FINE[0], 2, 1), (FEW_FINE[0], 3, 1),
                                          (FEW_FINE[1], 3, 1), (FEW_FINE[0], 8, 64), (FEW_FINE[1], 9, 64),
-                                         (FEW_FINE[2], 9, 0), (FEW_FINE[2], 21, 0)],
+                                         (FEW_FINE[2], 9, 0), (FEW_FINE[2], 21, 0), (MANY_FINE[0], 2, 64),
+                                         (MANY_FINE[1], 2, 64), (MANY_FINE[1], 3, 64)],
                          ids=lambda v: getattr(v, "name", str(v)))
 def test_tall_layers_with_few_chunks(spec, B, rows):
     """Where most of a workgroup's wavefronts would have no chunk, the kernel is slower than those it takes over from: the
     fp16 form (256-row tiles), or on layers with fine salient groups one batch-1 launch per row (rows = 1) or the generic
-    kernel (rows = 0). Sampled rows against the oracle."""
+    kernel (rows = 0); where they have enough, it is chosen. Sampled rows against the oracle."""
     from paper_2608_15602_amd import fluxbin as fb
     log(f"case few chunks {spec.name} B={B}")
     L = make_layer(spec)
