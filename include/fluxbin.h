@@ -218,8 +218,8 @@ fluxbin_status fluxbin_lut_gemv(const fluxbin_layer* layer, const uint16_t* d_x,
  * more) or B >= 80 (smaller ones; many-row matrix-core kernel; fewer than 512 last rows run as a call of these rows alone
  * would), else 16; T = 1 (B launches of the batch-1 kernels) for B <= 8 on mu = 8 layers with 8 or 16 fine salient
  * row-scale groups per chunk (the s16 / s8 configurations) of fewer than 8 M weights (24 M at B = 2), and on
- * larger ones where these launches are estimated to be faster (tall layers of few columns), unless the batch_tile tuning
- * asks for 16. fluxbin_plan_query reports T as batch_tile_rows.
+ * larger ones where these launches are estimated to be faster (few columns, or a nearly empty last wave of workgroups),
+ * unless the batch_tile tuning asks for 16. fluxbin_plan_query reports T as batch_tile_rows.
  * d_x fp16 with row stride ldx >= N (elements); d_y with row stride ldy >= M (elements of the output type). B = 1
  * gives the same result as fluxbin_lut_gemv.
  * Kernels: the LUT batch kernel (one set of tables per batch row; mu = 8, B <= 4 on layers with at least 2.25 (B = 2)

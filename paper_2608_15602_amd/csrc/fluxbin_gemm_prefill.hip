@@ -24,7 +24,8 @@
 //
 // us per call, 32-row launches of the small-batch kernel -> this, on one 256-CU device: 28672x8192 with 3 bases + 5%
 // B = 64 137 -> 112, B = 128 273 -> 192, B = 256 543 -> 336 (1.09 PFLOP/s; a large fp16 matrix product reaches 1.29 on
-// the same device), 8192x28672 B = 256 570 -> 339, 4096x4096 with 2 bases + 2% B = 256 146 -> 42.
+// the same device), 8192x28672 B = 256 570 -> 339, 4096x4096 with 2 bases + 2% B = 256 146 -> 42. Single calls apart from
+// each other; among others the clock is lower (a kernel trace over three layers, B = 256: 374, and 9 for the image).
 #include "fluxbin_device.h"
 #include "fluxbin_signs.h"
 

@@ -324,8 +324,9 @@ static int64_t mx_grid(const fluxbin_layer& L, const Derived& dv, int64_t cus, b
 // others the most units that one workgroup takes, the row scales' MB and the sums of a split tile. So the batch-1 launches
 // win where a last wave is nearly empty or a row tile has few chunks (66368x512 s8 B = 2 20.4 -> 32.5, B = 3 28.1 -> 42.7;
 // 132800x256 s16 B = 3 25.6 -> 41.4; 18432x4608 s8, 288 workgroups, B = 2 1.24 times as long), the block-scaled kernel
-// elsewhere (B = 3 2208x23808 s16, 4 bases, 62.0 -> 34.3; B = 2 5120x13824 s16 27.5 -> 20.1). The choice takes 1.003 times
-// as long as the better form of each call.
+// elsewhere (B = 3 2208x23808 s8, 4 bases, 62.0 -> 34.3; B = 2 5120x13824 s8 27.5 -> 20.1). The choice takes 1.003 times
+// as long as the better form of each call; over 900 calls on other layers 5 take more than 1.03 times the batch-1
+// launches' time (at worst 1.24), 23 more than 1.03 times the block-scaled kernel's (1.14).
 static bool mx_fine_small_batch(const fluxbin_layer& L, const Derived& dv, int B) {
   const int64_t MN = L.shape.M * L.shape.N;
   if (!salient_fine(L, dv) || B < 2 || MN < (B == 2 ? int64_t(24) << 20 : int64_t(8) << 20)) return false;
